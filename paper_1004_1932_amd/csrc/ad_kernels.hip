@@ -2654,7 +2654,7 @@ hipError_t launch_pairs(const Dev& d, const Epi& e, const Shape& sh, int mode, h
         return hipErrorInvalidValue;
     }
     /* AD_FP64: the terms spread over waves (work list of target blocks) */
-    if (e.prec == PREC_FP64 && d.nfitems > 0) {
+    if (e.prec == PREC_FP64 && d.nfitems > 0 && sh.fused == 0) {
         const int tw = f64w_targets(d.Ntot);
         if (tw == 4)
             return f64w_chunk(d.Ntot) == 128 ? go_f64w<4, 128>(d, e, sh, mode, s, tm)
