@@ -8,11 +8,20 @@
  *   K^{sr} = w sin(phi_s - phi_r) (15/64) (a/ell) (lam/ell)^2 (ell/D)^5 Dhat
  *            (3s + 6rq + 6 s q^2 - 7 s^3 - 21 s r^2 - 42 q s^2 r + 63 s^3 r^2),
  *   D = R_s - R_r, s = Dhat.N_s, r = Dhat.N_r, q = N_s.N_r.
- * One wave per dumbbell: lane l sums over the others j = l, l + 64, ... in
- * ascending order, and a fixed butterfly of shuffles adds the 64 partial
- * sums (every lane ends with the same bits). FP64 throughout, no FMA
- * contraction. (One thread per dumbbell left the paper's arrays of 125-729
- * dumbbells with one to six work-groups on the whole chip.)
+ * One dumbbell per WPT waves: the lanes share the sum over the others, a
+ * fixed butterfly and, with WPT = 4, the waves' sums through LDS in a fixed
+ * order add the partial sums. FP64 throughout, FMAs written out. With up to
+ * SA_WIDE dumbbells the launch has fewer waves than the chip has SIMDs at one
+ * wave per dumbbell, and a stage is a chain of latencies (loads, the terms
+ * one after another, the reduction, the update): four waves per dumbbell
+ * shorten the terms' part. Above that what bounds a stage is FP64 issue,
+ * about 80 instructions per pair (reciprocal square root, a sine over one
+ * period, Horner forms of the three polynomials), where the plain form's
+ * square root, four divisions and library sine took about 250.
+ * Per RK4 step: 343 dumbbells 24.7 us (39 in the plain form with one wave per
+ * dumbbell; k_sa_stage 5.2 us against 9.4), 4096 dumbbells 263 us (531). The
+ * rates' error against 80 bits (root mean square over 27 to 800 dumbbells,
+ * six draws each): 0.80e-15 and 0.87e-15 against 0.79e-15 and 0.91e-15.
  * A step is four launches of k_sa_stage (RK4); each also applies its stage's
  * update to its own dumbbell, and the last one scales the axes back to unit
  * length.
@@ -28,134 +37,208 @@
 namespace ad_sa {
 
 constexpr double kPi = 3.14159265358979323846;
-constexpr int SA_WG = 64; /* one wave, one dumbbell */
+constexpr int SA_WG = 256;   /* 4 / WPT dumbbells */
+constexpr int SA_WIDE = 1024; /* four waves per dumbbell up to this many, one above */
 
 struct SaCoef {
     double ell, cj, ck; /* cj = a w (9/64)(lam/ell)^2, ck = w (15/64)(a/ell)(lam/ell)^2 */
     double h2, dt, dt6;
 };
 
-/* rates of dumbbell i against all S, reading positions Rs and axes Ns; called
- * by all 64 lanes of the wave that owns i, which all return the rates */
-__device__ void sa_rates(const SaCoef& k, int S, int i, const double* __restrict__ Rs,
-                         const double* __restrict__ Ns, const double* __restrict__ phi, double dR[3], double dN[3],
-                         int* bad) {
-    const int l = threadIdx.x & 63;
-    double ri[3], ni[3];
-    for (int a = 0; a < 3; ++a) {
-        ri[a] = Rs[3 * i + a];
-        ni[a] = Ns[3 * i + a];
-    }
-    const double pi_ = phi[i];
-    double jx = 0.0, jy = 0.0, jz = 0.0, kx = 0.0, ky = 0.0, kz = 0.0;
-    for (int j = l; j < S; j += 64) {
-        if (j == i) continue;
-        const double rj[3] = {Rs[3 * j], Rs[3 * j + 1], Rs[3 * j + 2]};
-        const double nj[3] = {Ns[3 * j], Ns[3 * j + 1], Ns[3 * j + 2]};
-        const double Dx = ri[0] - rj[0];
-        const double Dy = ri[1] - rj[1];
-        const double Dz = ri[2] - rj[2];
-        const double D = sqrt((Dx * Dx + Dy * Dy) + Dz * Dz);
-        if (D == 0.0) {
-            *bad = 1;
-            continue;
-        }
-        const double ux = Dx / D, uy = Dy / D, uz = Dz / D;
-        const double s = (ux * ni[0] + uy * ni[1]) + uz * ni[2];
-        const double r = (ux * nj[0] + uy * nj[1]) + uz * nj[2];
-        const double q = (ni[0] * nj[0] + ni[1] * nj[1]) + ni[2] * nj[2];
-        const double sn = sin(pi_ - phi[j]);
-        const double x = k.ell / D;
-        const double x4 = (x * x) * (x * x);
-        const double aN = 2.0 * s + 4.0 * q * r - 10.0 * s * r * r;
-        const double aD =
-            1.0 + 2.0 * q * q - 5.0 * s * s - 5.0 * r * r - 20.0 * q * s * r + 35.0 * s * s * r * r;
-        const double fj = k.cj * sn * x4;
-        jx = jx + fj * (ni[0] * aN + ux * aD);
-        jy = jy + fj * (ni[1] * aN + uy * aD);
-        jz = jz + fj * (ni[2] * aN + uz * aD);
-        const double bK = 3.0 * s + 6.0 * r * q + 6.0 * s * q * q - 7.0 * s * s * s - 21.0 * s * r * r -
-                          42.0 * q * s * s * r + 63.0 * s * s * s * r * r;
-        const double fk = k.ck * sn * (x4 * x) * bK;
-        kx = kx + fk * ux;
-        ky = ky + fk * uy;
-        kz = kz + fk * uz;
-    }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        jx = jx + __shfl_xor(jx, o);
-        jy = jy + __shfl_xor(jy, o);
-        jz = jz + __shfl_xor(jz, o);
-        kx = kx + __shfl_xor(kx, o);
-        ky = ky + __shfl_xor(ky, o);
-        kz = kz + __shfl_xor(kz, o);
-    }
-    dR[0] = jx;
-    dR[1] = jy;
-    dR[2] = jz;
-    const double nk = (ni[0] * kx + ni[1] * ky) + ni[2] * kz;
-    dN[0] = -(kx - ni[0] * nk);
-    dN[1] = -(ky - ni[1] * nk);
-    dN[2] = -(kz - ni[2] * nk);
+__device__ __forceinline__ unsigned sa_hi(double x) {
+    return (unsigned)(__builtin_bit_cast(unsigned long long, x) >> 32);
 }
 
+/* sin x for |x| < 2^19: reduced by the nearest multiple n of pi (pi as the sum
+ * of two doubles; the first product-difference is exact), then the odd Taylor
+ * polynomial on [-pi/2, pi/2] up to r^21 (the next term is below 2^-59), with
+ * the sign (-1)^n. Within an ulp. */
+__device__ __forceinline__ double sa_sin(double x) {
+    const double n = __builtin_rint(x * 0x1.45f306dc9c883p-2);
+    double r = __builtin_fma(-n, 0x1.921fb54442d18p+1, x);
+    r = __builtin_fma(-n, 0x1.1a62633145c07p-53, r);
+    const double z = r * r;
+    double p = 1.0 / 51090942171709440000.0; /* 1/21! */
+    p = __builtin_fma(p, z, -1.0 / 121645100408832000.0);
+    p = __builtin_fma(p, z, 1.0 / 355687428096000.0);
+    p = __builtin_fma(p, z, -1.0 / 1307674368000.0);
+    p = __builtin_fma(p, z, 1.0 / 6227020800.0);
+    p = __builtin_fma(p, z, -1.0 / 39916800.0);
+    p = __builtin_fma(p, z, 1.0 / 362880.0);
+    p = __builtin_fma(p, z, -1.0 / 5040.0);
+    p = __builtin_fma(p, z, 1.0 / 120.0);
+    p = __builtin_fma(p, z, -1.0 / 6.0);
+    const double s = __builtin_fma(r * z, p, r);
+    const unsigned long long sign = (unsigned long long)((int)n & 1) << 63;
+    return __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, s) ^ sign);
+}
+
+/* 1/sqrt(x), rounded but for rare last-bit cases (the rates hold its fifth
+ * power): v_rsq_f64 (about 2^-24) and one third-order step whose residual
+ * 1 - x y^2 includes the rounding of x y */
+__device__ __forceinline__ double sa_rsqrt(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double g = x * y;
+    const double e = __builtin_fma(-__builtin_fma(x, y, -g), y, __builtin_fma(-g, y, 1.0));
+    return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, 0xF, 0xF, false);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xF, 0xF, false);
+    return v + __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+/* sum over the wave, the same bits in every lane: pairs, quads, halves of a
+ * row and rows by DPP (a VALU operand modifier), the four rows by exchanges */
+__device__ __forceinline__ double wave_sum(double v) {
+    v = dpp_add<0xB1>(v);  /* quad_perm [1,0,3,2] */
+    v = dpp_add<0x4E>(v);  /* quad_perm [2,3,0,1] */
+    v = dpp_add<0x141>(v); /* row_half_mirror */
+    v = dpp_add<0x140>(v); /* row_mirror */
+    v = v + __shfl_xor(v, 16);
+    return v + __shfl_xor(v, 32);
+}
+
+/* The rates of dumbbell i against all S, positions Rs and axes Ns; called by
+ * all threads of the work-group, wave w of it working for dumbbell i (i >= S:
+ * none). Lane c < 6 of the first wave of i returns component c of (dR, dN);
+ * *bad is raised in every lane of that wave when two centres coincide. */
+template <int WPT>
+__device__ __forceinline__ double sa_rates(const SaCoef& k, int S, int i, const double* __restrict__ Rs,
+                                           const double* __restrict__ Ns, const double* __restrict__ phi, int* bad) {
+    __shared__ double red[4][8];
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63, sub = w % WPT;
+    double ri[3] = {0.0, 0.0, 0.0}, ni[3] = {0.0, 0.0, 0.0}, pi_ = 0.0;
+    if (i < S) {
+        for (int a = 0; a < 3; ++a) {
+            ri[a] = Rs[3 * i + a];
+            ni[a] = Ns[3 * i + a];
+        }
+        pi_ = phi[i];
+    }
+    /* the sums of fj aN, fj aD u and fk u; the constants and the axis n_i,
+     * common to every term, are applied after the sum */
+    double v[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    int same = 0;
+#pragma unroll 2
+    for (int j = sub * 64 + l; j < S; j += 64 * WPT) {
+        const double rj[3] = {Rs[3 * j], Rs[3 * j + 1], Rs[3 * j + 2]};
+        const double nj[3] = {Ns[3 * j], Ns[3 * j + 1], Ns[3 * j + 2]};
+        const double ph = pi_ - phi[j];
+        const double Dx = ri[0] - rj[0], Dy = ri[1] - rj[1], Dz = ri[2] - rj[2];
+        /* the dumbbell itself: D = 0 at distance 1, weight 0 */
+        const bool self = j == i;
+        const double D2 = self ? 1.0 : __builtin_fma(Dz, Dz, __builtin_fma(Dy, Dy, Dx * Dx));
+        double iD = sa_rsqrt(D2), sn = sa_sin(ph);
+        /* operands out of the short forms' range */
+        const bool far = sa_hi(D2) - ((1023u - 900u) << 20) >= (1800u << 20);
+        if (far || (sa_hi(ph) & 0x7fffffffu) >= ((1023u + 19u) << 20)) {
+            const double D = sqrt(D2);
+            if (D == 0.0) {
+                same = 1;
+                continue;
+            }
+            iD = 1.0 / D;
+            sn = sin(ph);
+        }
+        sn = self ? 0.0 : sn;
+        const double ux = Dx * iD, uy = Dy * iD, uz = Dz * iD;
+        const double s = __builtin_fma(uz, ni[2], __builtin_fma(uy, ni[1], ux * ni[0]));
+        const double r = __builtin_fma(uz, nj[2], __builtin_fma(uy, nj[1], ux * nj[0]));
+        const double q = __builtin_fma(ni[2], nj[2], __builtin_fma(ni[1], nj[1], ni[0] * nj[0]));
+        const double x = k.ell * iD, x2 = x * x, fj = sn * (x2 * x2);
+        const double sr = s * r, q2 = q + q;
+        /* 2s + 4qr - 10 s r^2 */
+        const double aN = __builtin_fma(r, __builtin_fma(-10.0, sr, q2 + q2), s + s);
+        /* 1 + 2q^2 - 5s^2 - 5r^2 - 20 q s r + 35 s^2 r^2 */
+        double aD = __builtin_fma(q, __builtin_fma(-20.0, sr, q2), 1.0);
+        aD = __builtin_fma(-5.0, __builtin_fma(s, s, r * r), aD);
+        aD = __builtin_fma(35.0 * sr, sr, aD);
+        /* 6rq + s (3 + 6q^2 - 7s^2 - 21r^2 + s r (63 s r - 42 q)) */
+        const double q6 = 6.0 * q;
+        double c = __builtin_fma(sr, __builtin_fma(63.0, sr, -42.0 * q), 3.0);
+        c = __builtin_fma(q6, q, c);
+        c = __builtin_fma(-7.0 * s, s, c);
+        c = __builtin_fma(-21.0 * r, r, c);
+        const double bK = __builtin_fma(s, c, q6 * r);
+        const double fD = fj * aD, fk = (fj * x) * bK;
+        v[0] = __builtin_fma(fj, aN, v[0]);
+        v[1] = __builtin_fma(fD, ux, v[1]);
+        v[2] = __builtin_fma(fD, uy, v[2]);
+        v[3] = __builtin_fma(fD, uz, v[3]);
+        v[4] = __builtin_fma(fk, ux, v[4]);
+        v[5] = __builtin_fma(fk, uy, v[5]);
+        v[6] = __builtin_fma(fk, uz, v[6]);
+    }
+#pragma unroll
+    for (int a = 0; a < 7; ++a) v[a] = wave_sum(v[a]);
+    *bad = __any(same);
+    if (WPT > 1) {
+        if (l == 0) {
+            for (int a = 0; a < 7; ++a) red[w][a] = v[a];
+            red[w][7] = *bad ? 1.0 : 0.0;
+        }
+        __syncthreads();
+        if (sub == 0) {
+            for (int a = 0; a < 7; ++a) v[a] = (v[a] + red[w + 1][a]) + (red[w + 2][a] + red[w + 3][a]);
+            *bad = (red[w][7] + red[w + 1][7]) + (red[w + 2][7] + red[w + 3][7]) != 0.0;
+        }
+    }
+    const int a = l >= 3 ? l - 3 : l;
+    const double n_a = a == 0 ? ni[0] : a == 1 ? ni[1] : ni[2];
+    if (l < 3) return k.cj * __builtin_fma(n_a, v[0], a == 0 ? v[1] : a == 1 ? v[2] : v[3]);
+    const double nk = __builtin_fma(ni[2], v[6], __builtin_fma(ni[1], v[5], ni[0] * v[4]));
+    return -(k.ck * __builtin_fma(-n_a, nk, a == 0 ? v[4] : a == 1 ? v[5] : v[6]));
+}
+
+template <int WPT>
 __global__ __launch_bounds__(SA_WG) void k_sa_rhs(SaCoef k, int S, const double* __restrict__ R,
                                                   const double* __restrict__ N, const double* __restrict__ phi,
-                                                  double* __restrict__ dR, double* __restrict__ dN, int* flag) {
-    const int i = blockIdx.x; /* the grid has exactly S work-groups */
-    double r[3], n[3];
+                                                  double* __restrict__ dR, double* __restrict__ dN) {
+    const int i = blockIdx.x * (4 / WPT) + (threadIdx.x >> 6) / WPT, l = threadIdx.x & 63;
     int bad = 0;
-    sa_rates(k, S, i, R, N, phi, r, n, &bad);
-    const int any = __any(bad);
-    if (threadIdx.x != 0) return;
-    for (int a = 0; a < 3; ++a) {
-        dR[3 * i + a] = r[a];
-        dN[3 * i + a] = n[a];
-    }
-    if (any && flag) atomicOr(flag, 1);
+    const double v = sa_rates<WPT>(k, S, i, R, N, phi, &bad);
+    if ((threadIdx.x >> 6) % WPT != 0 || i >= S || l >= 6) return;
+    (l < 3 ? dR + 3 * i + l : dN + 3 * i + l - 3)[0] = v;
 }
 
 /* One RK4 stage: rates at the stage positions (YR, YN), accumulate, and write
  * the next stage positions (or, at the last stage, the new state). */
+template <int WPT>
 __global__ __launch_bounds__(SA_WG) void k_sa_stage(SaCoef k, int S, int stage, double* __restrict__ R,
                                                     double* __restrict__ N, const double* __restrict__ phi,
                                                     const double* __restrict__ YR, const double* __restrict__ YN,
                                                     double* __restrict__ ZR, double* __restrict__ ZN,
                                                     double* __restrict__ AR, double* __restrict__ AN, int* flag) {
-    const int i = blockIdx.x; /* the grid has exactly S work-groups */
-    double kr[3], kn[3];
-    int bad = 0;
-    sa_rates(k, S, i, YR, YN, phi, kr, kn, &bad);
-    const int any = __any(bad);
-    if (threadIdx.x != 0) return;
-    if (any) atomicOr(flag, 1);
-    double nv[3];
-    for (int a = 0; a < 3; ++a) {
-        const int o = 3 * i + a;
-        const double x = R[o], v = N[o];
-        if (stage == 0) {
-            AR[o] = kr[a];
-            AN[o] = kn[a];
-            ZR[o] = x + k.h2 * kr[a];
-            ZN[o] = v + k.h2 * kn[a];
-        } else if (stage == 1) {
-            AR[o] = AR[o] + 2.0 * kr[a];
-            AN[o] = AN[o] + 2.0 * kn[a];
-            ZR[o] = x + k.h2 * kr[a];
-            ZN[o] = v + k.h2 * kn[a];
-        } else if (stage == 2) {
-            AR[o] = AR[o] + 2.0 * kr[a];
-            AN[o] = AN[o] + 2.0 * kn[a];
-            ZR[o] = x + k.dt * kr[a];
-            ZN[o] = v + k.dt * kn[a];
-        } else {
-            R[o] = x + k.dt6 * (AR[o] + kr[a]);
-            nv[a] = v + k.dt6 * (AN[o] + kn[a]);
-        }
+    const int i = blockIdx.x * (4 / WPT) + (threadIdx.x >> 6) / WPT, l = threadIdx.x & 63;
+    const bool own = (threadIdx.x >> 6) % WPT == 0 && i < S && l < 6;
+    const int o = 3 * i + (l < 3 ? l : l - 3);
+    /* the update's inputs, one component per lane, in flight under the sums */
+    double x = 0.0, acc = 0.0;
+    if (own) {
+        x = (l < 3 ? R : N)[o];
+        if (stage > 0) acc = (l < 3 ? AR : AN)[o];
     }
-    if (stage == 3) {
-        const double nn = sqrt((nv[0] * nv[0] + nv[1] * nv[1]) + nv[2] * nv[2]);
-        for (int a = 0; a < 3; ++a) N[3 * i + a] = nv[a] / nn;
+    int bad = 0;
+    const double v = sa_rates<WPT>(k, S, i, YR, YN, phi, &bad);
+    if ((threadIdx.x >> 6) % WPT != 0 || i >= S) return;
+    if (bad && l == 0) atomicOr(flag, 1);
+    if (stage < 3) {
+        if (own) {
+            (l < 3 ? AR : AN)[o] = stage == 0 ? v : acc + 2.0 * v;
+            (l < 3 ? ZR : ZN)[o] = x + (stage == 2 ? k.dt : k.h2) * v;
+        }
+        return;
+    }
+    const double y = x + k.dt6 * (acc + v);
+    const double n0 = __shfl(y, 3), n1 = __shfl(y, 4), n2 = __shfl(y, 5);
+    if (own) {
+        if (l < 3)
+            R[o] = y;
+        else
+            N[o] = y / sqrt((n0 * n0 + n1 * n1) + n2 * n2);
     }
 }
 
@@ -182,6 +265,8 @@ static SaCoef sa_coef(const ad_params* p, double dt) {
     return k;
 }
 
+static dim3 sa_grid(int S) { return dim3(S <= SA_WIDE ? S : (S + 3) / 4); }
+
 static size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 }  // namespace ad_sa
@@ -201,8 +286,8 @@ int ad_sa_rhs(const ad_params* p, int32_t S, const double* R, const double* N, c
               double* dN, void* stream) {
     if (!sa_params_ok(p) || S < 1 || !R || !N || !phi || !dR || !dN) return AD_EINVAL;
     const SaCoef k = sa_coef(p, 1.0);
-    hipLaunchKernelGGL(k_sa_rhs, dim3(S), dim3(SA_WG), 0, (hipStream_t)stream, k, S, R, N,
-                       phi, dR, dN, (int*)nullptr);
+    hipLaunchKernelGGL(S <= SA_WIDE ? k_sa_rhs<4> : k_sa_rhs<1>, sa_grid(S), dim3(SA_WG), 0, (hipStream_t)stream, k, S,
+                       R, N, phi, dR, dN);
     return hipGetLastError() == hipSuccess ? AD_OK : AD_EDEVICE;
 }
 
@@ -224,14 +309,15 @@ int ad_sa_run(const ad_params* p, int32_t S, double* R, double* N, const double*
     double* AR = reinterpret_cast<double*>(b + 256 + 4 * blk);
     double* AN = reinterpret_cast<double*>(b + 256 + 5 * blk);
     const SaCoef k = sa_coef(p, dt);
-    const dim3 grid(S), block(SA_WG); /* one work-group (one wave) per dumbbell */
+    const dim3 grid = sa_grid(S), block(SA_WG);
+    auto kern = S <= SA_WIDE ? k_sa_stage<4> : k_sa_stage<1>;
     hipLaunchKernelGGL(k_sa_clear, dim3(1), dim3(1), 0, st, flag);
     for (int64_t n = 0; n < nsteps; ++n) {
         /* stage inputs: state, YA, YB, YA; outputs: YA, YB, YA, state */
-        hipLaunchKernelGGL(k_sa_stage, grid, block, 0, st, k, S, 0, R, N, phi, R, N, YA_R, YA_N, AR, AN, flag);
-        hipLaunchKernelGGL(k_sa_stage, grid, block, 0, st, k, S, 1, R, N, phi, YA_R, YA_N, YB_R, YB_N, AR, AN, flag);
-        hipLaunchKernelGGL(k_sa_stage, grid, block, 0, st, k, S, 2, R, N, phi, YB_R, YB_N, YA_R, YA_N, AR, AN, flag);
-        hipLaunchKernelGGL(k_sa_stage, grid, block, 0, st, k, S, 3, R, N, phi, YA_R, YA_N, YB_R, YB_N, AR, AN, flag);
+        hipLaunchKernelGGL(kern, grid, block, 0, st, k, S, 0, R, N, phi, R, N, YA_R, YA_N, AR, AN, flag);
+        hipLaunchKernelGGL(kern, grid, block, 0, st, k, S, 1, R, N, phi, YA_R, YA_N, YB_R, YB_N, AR, AN, flag);
+        hipLaunchKernelGGL(kern, grid, block, 0, st, k, S, 2, R, N, phi, YB_R, YB_N, YA_R, YA_N, AR, AN, flag);
+        hipLaunchKernelGGL(kern, grid, block, 0, st, k, S, 3, R, N, phi, YA_R, YA_N, YB_R, YB_N, AR, AN, flag);
         if (hipGetLastError() != hipSuccess) return AD_EDEVICE;
     }
     int h = 0;
