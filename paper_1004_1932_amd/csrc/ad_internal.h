@@ -99,6 +99,7 @@ struct Dev {
     const Item* fitems; /* fused stages of an ensemble: (system, target block) items; the
                            resident form: one per system; AD_FP64 pair sum: target blocks */
     int nfitems;        /* 0: one system, blocks in order */
+    int f64_blocks;     /* 1: fitems are the AD_FP64 pair sum's target blocks */
     const long long* sys_hbase; /* [nsys] dense mode: first element of the system's tensor */
     const double* tab;  /* [ring][8] (sin, cos) of omega*t per epilogue stage */
     int ring;           /* entries in tab, a power of two (rows are step & (ring - 1)) */
@@ -236,20 +237,32 @@ __host__ __device__ inline int fused_wide_lds_bytes(int n, int split) {
     const int red = 4 * FW_I * 6 * 4 + FW_I * 3 * 8 + 16;
     return b > red ? b : red;
 }
-/* AD_FP64 pair sum with producer and consumer waves (k_pairs_f64w):
- * producer waves per work-group (one, two and three measured at N = 512 to
- * 8192: one was fastest everywhere, by 4 to 12 %); targets per work-group,
- * about Ntot / 1024 from 1 to 4, so that the launch holds about two waves per
- * SIMD; sources per chunk: 128 where a launch of 4-target work-groups holds
- * at most one producer wave per SIMD (Ntot below 8192: 7 % faster at 4096,
- * more independent terms per lane), else 64 (at 8192 the larger chunk's
- * registers cost a wave per SIMD, 48 % slower) */
-constexpr int F64W_NP = 1;
-__host__ __device__ inline int f64w_targets(int Ntot) { return Ntot >= 4096 ? 4 : Ntot >= 2048 ? 2 : 1; }
-__host__ __device__ inline int f64w_chunk(int Ntot) { return f64w_targets(Ntot) == 4 && Ntot < 8192 ? 128 : 64; }
-/* LDS of a work-group: two sets of F64W_NP chunk buffers of rows x (cw + 1) */
-__host__ __device__ inline int f64w_lds_bytes(int tw, int rpy, int cw) {
-    return 2 * F64W_NP * (rpy ? 6 : 3) * tw * (cw + 1) * 8;
+/* AD_FP64 pair sum with producer and consumer waves (k_pairs_f64w): targets
+ * per work-group, producer waves, sources per chunk. Larger blocks spend less
+ * on the consumer (its additions are the same for 2 or 4 targets), so the
+ * largest shape is taken that still fills the chip, and whose work-groups
+ * are all resident at once: by registers and LDS a compute unit holds 4 of
+ * {4,1,128}, 5 of {4,2,64}, 6 of {2,1,128} and 8 of {4,1,64} (RPY, six
+ * components in LDS: 3, 3, 6 and 6), which is where the lines lie. us per RK4
+ * step, Oseen, in the order {2,2,64}, {2,1,128}, {4,1,128}, {4,2,64},
+ * {4,1,64}: N = 1024 37, 56, 70, 53, 77 (before the kernel closed the stage);
+ * 2048 94, 77, 101, 85, 117; 4096 -, 306, 193, 214, 222; 5000 -, 430, 458,
+ * 315, 374; 8192 -, 999, 970, 784, 689; 16384 -, 3612, 3536, 2860, 3021. RPY,
+ * from {2,1,128}: 3072 174, 183, 180, 202; 6144 701, 880, 652, 597; 8192
+ * 1195, 1537, 1120, 1303; 16384 4367, 5552, 4234, 4180. */
+struct F64WShape {
+    int tw, np, cw; /* targets, producer waves, sources per chunk */
+};
+__host__ __device__ inline F64WShape f64w_shape(int Ntot, int rpy) {
+    if (Ntot <= 1536) return {2, 2, 64};
+    if (Ntot <= (rpy ? 3072 : 2560)) return {2, 1, 128};
+    if (rpy) return Ntot > 6144 && Ntot <= 8192 ? F64WShape{4, 2, 64} : F64WShape{4, 1, 64};
+    if (Ntot <= 4096) return {4, 1, 128};
+    return Ntot > 5120 && Ntot <= 8192 ? F64WShape{4, 1, 64} : F64WShape{4, 2, 64};
+}
+/* LDS of a work-group: two sets of np chunk buffers of rows x (cw + 2) */
+__host__ __device__ inline int f64w_lds_bytes(const F64WShape& f, int rpy) {
+    return 2 * f.np * (rpy ? 6 : 3) * f.tw * (f.cw + 2) * 8;
 }
 /* the most target spheres per work-group of the streamed fused stage */
 constexpr int FT_I = 16;
@@ -345,6 +358,13 @@ hipError_t launch_resident(const Dev& d, const Epi& e, int hilo, int maxNb, long
 hipError_t prepare_fused();
 hipError_t launch_fused(const Dev& d, const Epi& e, const Shape& sh, int maxNb, hipStream_t s,
                         hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+/* AD_FP64's pair kernel over its work list of target blocks (k_pairs_f64w)
+ * also closes the stage or the product; with steric forces the epilogue
+ * follows, as after every other pair kernel */
+inline bool pairs_close(const Dev& d, const Epi& e) {
+    return e.prec == PREC_FP64 && d.f64_blocks && (e.u_aos || e.pack_next);
+}
+/* does nothing where pairs_close */
 hipError_t launch_epilogue(const Dev& d, const Epi& e, hipStream_t s);
 /* steric forces at stage positions Y, then the next pack (steric path) */
 hipError_t launch_steric_pack(const Dev& d, const Coef& c, int prec, hipStream_t s);

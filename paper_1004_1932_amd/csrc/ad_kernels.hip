@@ -1469,9 +1469,8 @@ __global__ __launch_bounds__(64 * NW, 8) void k_stage_stream_x2(Dev d, Epi e) {
 /* FP64 streamed form of the fused stage (AD_FP64_TILED with
  * ad_launch.fused = 3): k_stage_stream's work-group shape, streaming and
  * combination order in FP64 arithmetic, for a like-for-like comparison with
- * the FP32C form. The pair term uses v_rsq_f64 refined by one Newton step
- * and FMAs (a relative error of a few ulp, not the IEEE sqrt and divisions
- * of the plain sum); the partial sums are plain FP64 sums. As in the other
+ * the FP32C form. The pair term uses a refined v_rsq_f64 and FMAs (not the
+ * IEEE sqrt and divisions of the plain sum); the partial sums are plain FP64 sums. As in the other
  * FP64 forms, the pair sum includes the dumbbell partner and only the self
  * term is masked, u0 is the self term alone, and the pack is the FP64 one
  * (3 double2 per sphere). */
@@ -1495,11 +1494,15 @@ __device__ __forceinline__ void pair_term64(double ir, double rx, double ry, dou
     }
 }
 
-/* 1/sqrt(r2) from v_rsq_f64 and one Newton step y (1 + (1 - r2 y^2) / 2) */
-__device__ __forceinline__ double rsqrt64_nr(double r2) {
+/* 1/sqrt(r2) from v_rsq_f64 (about 2^-24) and one third-order step
+ * y (1 + e/2 + 3 e^2/8), e = 1 - r2 y^2: within an ulp. (One Newton step, two
+ * instructions fewer, leaves 4e-15.) */
+__device__ __forceinline__ double rsqrt64(double r2) {
     const double y = __builtin_amdgcn_rsq(r2);
-    const double e = __builtin_fma(-r2 * y, y, 1.0);
-    return __builtin_fma(0.5 * y, e, y);
+    const double g = r2 * y;
+    const double e = __builtin_fma(-g, y, 1.0);
+    const double p = __builtin_fma(e, 0.375, 0.5);
+    return __builtin_fma(y * e, p, y);
 }
 
 template <int RPY, int TI>
@@ -1584,7 +1587,7 @@ __global__ __launch_bounds__(1024) void k_stage_stream64(Dev d, Epi e) {
         const double2 Fj = sF[x];
         const double rx = hx - Aj.x, ry = hy - Aj.y, rz = hz - Aj.z;
         const double r2 = __builtin_fma(rz, rz, __builtin_fma(ry, ry, rx * rx));
-        double ir = rsqrt64_nr(r2);
+        double ir = rsqrt64(r2);
         if (masked && j == i - off) ir = 0.0;
         pair_term64<RPY>(ir, rx, ry, rz, Aj.w, Fj.x, Fj.y, crr, px, py, pz);
     };
@@ -1660,14 +1663,97 @@ __global__ __launch_bounds__(1024) void k_stage_stream64(Dev d, Epi e) {
     }
 }
 
+/* The correctly rounded FP64 quotients of a pair term, sharing work between
+ * them: s = sqrt(r2), ir = 1/s, t = fr/r2 and (RPY) ir/r2, each bit for bit
+ * the IEEE result of the plain expression.
+ *   s: v_rsq_f64 (about 2^-24) refined on g = sqrt(x) and h = 1/(2 sqrt(x)),
+ *     then corrected twice by its exact residual x - g^2;
+ *   1/s starts from 2h (already within 2^-46) in place of a v_rcp_f64 and a
+ *     first Newton step: one step, then the correction by the exact residual
+ *     1 - s y, after which the quotient is the rounded one (Markstein, "Computation
+ *     of elementary functions on the IBM RISC System/6000 processor", 1990)
+ *     unless the divisor's significand is all ones;
+ *   1/r2 starts from (2h)^2 (within 2^-45): one Newton step, then the quotient
+ *     a y corrected once by its residual a - r2 q, rounded under the same
+ *     condition on r2.
+ * 21 FP64 instructions and one transcendental in place of the compiler's 39
+ * and three for the same three values (its square root and divisions also
+ * scale the exponents and fix up special operands), and a dependent chain of
+ * 15 for both quotients. They hold where no intermediate can leave the normal
+ * range: r2 in [2^-400, 2^400) and |fr| zero or in [2^-500, 2^500), and where
+ * neither s nor r2 has an all-ones low word; the callers test that (Range64)
+ * and take the plain expressions otherwise. (Checked on the CPU with fma for 2.1e9
+ * operands, hard cases among them; the parity tests compare whole
+ * trajectories.) */
+__device__ __forceinline__ unsigned lo_word(double x) {
+    return (unsigned)__builtin_bit_cast(unsigned long long, x);
+}
+__device__ __forceinline__ unsigned hi_word(double x) {
+    return (unsigned)(__builtin_bit_cast(unsigned long long, x) >> 32);
+}
+/* The range test over a lane's terms, on high words with 32-bit min and max
+ * (an FP64 compare with its select measured 48 cycles per wave, a 32-bit
+ * min or max 4): r2 in [2^-400, 2^400) (it is a sum of squares, so its sign
+ * bit is clear unless it is NaN, whose high word is larger), |fr| in
+ * [2^-500, 2^500), no all-ones low word of s or r2. A zero fr, which needs
+ * nothing, counts as too small: zeros() tells it apart. */
+struct Range64 {
+    unsigned rmin = 0xffffffffu, rmax = 0, fmin = 0xffffffffu, fmax = 0, ones = 0;
+    static constexpr unsigned kR2Lo = (1023u - 400u) << 20, kR2Hi = (1023u + 400u) << 20;
+    static constexpr unsigned kFrLo = (1023u - 500u) << 21, kFrHi = (1023u + 500u) << 21;
+    __device__ __forceinline__ void r2(double x) {
+        rmin = min(rmin, hi_word(x));
+        rmax = max(rmax, hi_word(x));
+    }
+    __device__ __forceinline__ void fr(double x) {
+        const unsigned h = hi_word(x) << 1; /* without the sign */
+        fmin = min(fmin, h);
+        fmax = max(fmax, h);
+    }
+    __device__ __forceinline__ bool ok_r2() const { return rmin >= kR2Lo && rmax < kR2Hi; }
+    __device__ __forceinline__ bool ok() const { return ok_r2() && fmax < kFrHi && ones != 0xffffffffu; }
+    __device__ __forceinline__ bool small_fr() const { return fmin < kFrLo; }
+    /* zero, or not too small */
+    static __device__ __forceinline__ bool fr_fits(double x) {
+        const unsigned h = hi_word(x) << 1;
+        return (h | lo_word(x)) == 0 || h >= kFrLo;
+    }
+};
+/* ir = 1/sqrt(x) as the plain expression rounds it, and y = 1/x (rounded but
+ * for rare last-bit cases) for div_exact; ones is raised to 0xffffffff where
+ * the short forms do not hold (s or x with an all-ones low word) */
+__device__ __forceinline__ void rcp_sqrt_exact(double x, double& ir, double& y, unsigned& ones) {
+    const double v = __builtin_amdgcn_rsq(x);
+    double g = x * v;
+    double h = v * 0.5;
+    double e = __builtin_fma(-h, g, 0.5);
+    g = __builtin_fma(g, e, g);
+    h = __builtin_fma(h, e, h);
+    double q = __builtin_fma(-g, g, x);
+    g = __builtin_fma(q, h, g);
+    q = __builtin_fma(-g, g, x);
+    const double s = __builtin_fma(q, h, g);
+    ones = max(ones, max(lo_word(s), lo_word(x)));
+    const double h2 = h + h;
+    y = h2 * h2;
+    y = __builtin_fma(y, __builtin_fma(-x, y, 1.0), y);
+    ir = __builtin_fma(h2, __builtin_fma(-s, h2, 1.0), h2);
+    ir = __builtin_fma(ir, __builtin_fma(-s, ir, 1.0), ir);
+}
+/* a/x as IEEE division rounds it, y from rcp_sqrt_exact */
+__device__ __forceinline__ double div_exact(double a, double x, double y) {
+    const double q = a * y;
+    return __builtin_fma(__builtin_fma(-x, q, a), y, q);
+}
+
 /* FP64: the sum in ascending j with the plain operation order
  *   r2 = (rx*rx + ry*ry) + rz*rz; ir = 1/sqrt(r2); fr = (rx*Fx + ry*Fy) + rz*Fz;
  *   t = fr/r2; acc = acc + ir*(F + t*r)
  * over every j != i of the chunk (partner included). A coincident pair is
  * skipped and raises the flag. With one chunk per system this is the
  * sequential FP64 sum exactly (AD_FP64 runs k_pairs_f64w, which gives the
- * same bits); AD_FP64_TILED runs several chunks. With RPY the correction
- * (F - 3 t r) ir/r2 is summed in a second accumulator. */
+ * same bits); AD_FP64_TILED runs several chunks. With RPY the correction (F - 3 t r) ir/r2 is
+ * summed in a second accumulator. */
 template <int WG, int IPL, int RPY>
 __global__ __launch_bounds__(WG) void k_pairs_f64(Dev d, Epi e, int mode) {
     __shared__ double2 sD[3][WG];
@@ -1767,41 +1853,6 @@ __global__ __launch_bounds__(WG) void k_pairs_f64(Dev d, Epi e, int mode) {
     }
 }
 
-/* Correctly rounded FP64 square root and division in their short forms.
- * The compiler's forms of sqrt(x) and a / b scale the operands' exponents
- * where an intermediate could leave the normal range and fix up special
- * operands (zero, infinity, NaN) afterwards; between those steps they are
- * exactly these instruction sequences (the square root: v_rsq_f64 refined
- * by Newton steps on g = sqrt(x) and h = 1 / (2 sqrt(x)); the division:
- * v_rcp_f64 refined twice, then the quotient corrected once by its
- * residual). For operands where no scaling or fixup applies they give the
- * same bits, which f64_plain_range guarantees with a wide margin: every
- * operand in [2^-400, 2^400], so that no intermediate gets near the ends of
- * the exponent range. */
-__device__ __forceinline__ bool f64_plain_range(double x) { return x >= 0x1p-400 && x <= 0x1p400; }
-__device__ __forceinline__ double sqrt_plain(double x) {
-    const double y = __builtin_amdgcn_rsq(x);
-    double g = x * y;
-    double h = y * 0.5;
-    const double r = __builtin_fma(-h, g, 0.5);
-    g = __builtin_fma(g, r, g);
-    h = __builtin_fma(h, r, h);
-    double d = __builtin_fma(-g, g, x);
-    g = __builtin_fma(d, h, g);
-    d = __builtin_fma(-g, g, x);
-    return __builtin_fma(d, h, g);
-}
-__device__ __forceinline__ double div_plain(double a, double b) {
-    double y = __builtin_amdgcn_rcp(b);
-    double e = __builtin_fma(-b, y, 1.0);
-    y = __builtin_fma(y, e, y);
-    e = __builtin_fma(-b, y, 1.0);
-    y = __builtin_fma(y, e, y);
-    const double q = a * y;
-    const double r = __builtin_fma(-b, q, a);
-    return __builtin_fma(r, y, q);
-}
-
 /* Work-group barrier that orders LDS only: vector-memory loads in flight
  * (the step table's next row, the next chunk's sources) are not waited for. */
 __device__ __forceinline__ void lds_barrier() {
@@ -1817,8 +1868,10 @@ __device__ __forceinline__ void lds_barrier() {
  * target) by columns (the chunk's sources); its consumer wave adds them,
  * lane r row r, to a running sum in ascending j. Chunks go in rounds of NP,
  * one per producer, through two sets of buffers: the producers form round
- * m + 1 while the consumer adds round m, and one LDS barrier ends a round
- * (one producer, F64W_NP, measured fastest).
+ * m + 1 while the consumer adds round m, and one LDS barrier ends a round.
+ * Unless steric forces are on, the consumer, which then holds every sum of
+ * its targets, also closes the stage or the product: no partial sums, no
+ * second launch (4.7 us per stage at N = 4096).
  * The terms are the plain sum's expressions and the additions its sequence,
  * so the result is bitwise k_pairs_f64's with one chunk per system. The
  * self term, a coincident pair (which raises the flag) and the padding past
@@ -1830,10 +1883,11 @@ template <int TW, int NP, int CW, int RPY>
 __global__ __launch_bounds__(64 * (NP + 1)) void k_pairs_f64w(Dev d, Epi e, int mode) {
     constexpr int NC = RPY ? 6 : 3;
     constexpr int ROWS = NC * TW;
-    constexpr int RS = CW + 1;          /* LDS row stride in doubles: odd, so the rows' reads of one
-                                           column fall in different banks */
+    constexpr int RS = CW + 2;          /* LDS row stride in doubles: pairs of columns are 16-byte
+                                           aligned, and the rows' reads of a pair fall in different
+                                           banks (4 mod 64) */
     constexpr int BUF = ROWS * RS; /* doubles per chunk buffer */
-    extern __shared__ double w_lds[];   /* [2 sets][NP chunks][ROWS][RS] */
+    extern __shared__ __align__(16) double w_lds[]; /* [2 sets][NP chunks][ROWS][RS] */
     const Item it = d.fitems[blockIdx.x];
     if (mode) advance_slots(d, e);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1845,19 +1899,106 @@ __global__ __launch_bounds__(64 * (NP + 1)) void k_pairs_f64w(Dev d, Epi e, int 
         /* the consumer */
         const int r = l < ROWS ? l : ROWS - 1;
         double acc = 0.0;
+        /* inputs of the closing, loaded first: lane a TW + q owns component a
+         * of target q, lane q < ni the phase of dumbbell q / 2 */
+        const bool close = e.u_aos || e.pack_next;
+        const int ca = l / TW, ci = it.i0 + (l - ca * TW);
+        const bool cl = l < 3 * TW && l - ca * TW < it.ni;
+        double u0 = 0.0, xv = 0.0, rv = 0.0, st = 0.0, ct = 0.0;
+        double2 tp = make_double2(0.0, 0.0);
+        long long step = 0;
+        if (close) {
+            if (cl) {
+                const int o = ca * d.Ntot + ci;
+                u0 = d.U0[o];
+                if (!e.u_aos) {
+                    xv = d.X[o];
+                    if (e.stage > 0) rv = d.R[o];
+                }
+            }
+            if (!e.u_aos) {
+                step = d.ctl->slot[e.stage > 0];
+                const long long row = step & (d.ring - 1);
+                if (l < it.ni) {
+                    st = d.tab[row * 8 + 2 * e.stage];
+                    ct = d.tab[row * 8 + 2 * e.stage + 1];
+                    tp = d.phitrig[(it.i0 >> 1) + (l >> 1)];
+                }
+            }
+        }
         lds_barrier();
         for (int m = 0; m < M; ++m) {
             const double* S = w_lds + (m & 1) * NP * BUF + r * RS;
             for (int p = 0; p < NP && m * NP + p < nch; ++p) {
-                const double* Ta = S + p * BUF;
+                /* two columns per read, a batch of reads ahead of the
+                 * additions (9.6 cycles per column against 16.1 one column
+                 * at a time; the dependent additions alone take 7.3) */
+                const double2* Ta = reinterpret_cast<const double2*>(S + p * BUF);
+                constexpr int B = 8;
+                double2 v[B];
 #pragma unroll
-                for (int u = 0; u < CW; ++u) acc = acc + Ta[u];
+                for (int u = 0; u < B; ++u) v[u] = Ta[u];
+#pragma unroll
+                for (int c = 0; c < CW / 2; c += B) {
+                    double2 nx[B];
+#pragma unroll
+                    for (int u = 0; u < B; ++u) nx[u] = (c + B < CW / 2) ? Ta[c + B + u] : v[u];
+#pragma unroll
+                    for (int u = 0; u < B; ++u) {
+                        acc = acc + v[u].x;
+                        acc = acc + v[u].y;
+                    }
+#pragma unroll
+                    for (int u = 0; u < B; ++u) v[u] = nx[u];
+                }
             }
             lds_barrier();
         }
-        if (l < ROWS) {
-            const int a = l / TW, q = l - a * TW;
-            if (q < it.ni) d.part[d.sys_pbase[it.sys] + (long long)a * Nb + (it.i0 + q - off)] = acc;
+        if (!close) {
+            /* steric forces on: the epilogue and the steric kernel close */
+            if (l < ROWS) {
+                const int a = l / TW, q = l - a * TW;
+                if (q < it.ni) d.part[d.sys_pbase[it.sys] + (long long)a * Nb + (it.i0 + q - off)] = acc;
+            }
+            return;
+        }
+        /* The consumer holds every sum of its targets: it closes the stage
+         * (or the product) as the epilogue does, in the epilogue's order. */
+        const double corr = RPY ? __shfl(acc, (l + 3 * TW) & 63) : 0.0;
+        double y = 0.0;
+        int nf = 0;
+        if (cl) {
+            double k = u0 + e.c.co * acc;
+            if (RPY) k = k + e.c.cr * corr;
+            nf = !isfinite(k);
+            if (e.u_aos)
+                e.u_aos[3 * ci + ca] = k;
+            else
+                y = stage_update(d, e, ca * d.Ntot + ci, ci, ca, k, xv, rv, step);
+        }
+        if (__any(nf) && l == 0) atomicOr(&d.ctl->flag, FLAG_NONFINITE);
+        if (e.u_aos) return;
+        /* lane q < TW: sphere q; both lanes of a dumbbell evaluate the same
+         * forces */
+        const int pq = l & (TW - 1), q0 = pq & ~1;
+        double y0[3], y1[3], f0[3], f1[3];
+        for (int a = 0; a < 3; ++a) {
+            y0[a] = __shfl(y, a * TW + q0);
+            y1[a] = __shfl(y, a * TW + q0 + 1);
+        }
+        if (l < it.ni) {
+            spring_forces(e.c, y0, y1, tp.x, tp.y, st, ct, f0, f1);
+            const int i = it.i0 + l;
+            const bool up = l & 1;
+            double ys[3], fs[3];
+            for (int a = 0; a < 3; ++a) {
+                ys[a] = up ? y1[a] : y0[a];
+                fs[a] = up ? f1[a] : f0[a];
+                d.U0[a * d.Ntot + i] = e.c.cs * fs[a];
+            }
+            d.pD2[3 * i + 0] = make_double2(ys[0], ys[1]);
+            d.pD2[3 * i + 1] = make_double2(ys[2], fs[0]);
+            d.pD2[3 * i + 2] = make_double2(fs[1], fs[2]);
         }
         return;
     }
@@ -1886,38 +2027,77 @@ __global__ __launch_bounds__(64 * (NP + 1)) void k_pairs_f64w(Dev d, Epi e, int 
             s2[u] = d.pD[3 * j + 2];
         }
     };
-    auto form = [&](int k, double* Tb0) {
-        double rx[U][TW], ry[U][TW], rz[U][TW], r2s[U][TW], ir[U][TW];
-        bool skip[U][TW];
-        int safe = 1;
-#pragma unroll
+    /* The terms of chunk k by the plain expressions, for any operands. */
+    auto form_plain = [&](int k, double* Tb0) {
+#pragma unroll 1
         for (int u = 0; u < U; ++u) {
             const int lj = k * CW + u * 64 + l;
             const bool in = lj < Nb;
-            const int j = off + lj;
+            double* Tb = Tb0 + u * 64 + l;
+            const double xj = u ? s0[U - 1].x : s0[0].x, yj = u ? s0[U - 1].y : s0[0].y;
+            const double zj = u ? s1[U - 1].x : s1[0].x, Fx = u ? s1[U - 1].y : s1[0].y;
+            const double Fy = u ? s2[U - 1].x : s2[0].x, Fz = u ? s2[U - 1].y : s2[0].y;
+#pragma unroll
+            for (int q = 0; q < TW; ++q) {
+                const double r[3] = {xi[q] - xj, yi[q] - yj, zi[q] - zj};
+                const double F[3] = {Fx, Fy, Fz};
+                const double r2 = (r[0] * r[0] + r[1] * r[1]) + r[2] * r[2];
+                const bool self = off + lj == iq[q];
+                double t[3] = {0.0, 0.0, 0.0}, v[3] = {0.0, 0.0, 0.0};
+                if (in && !self && r2 != 0.0) {
+                    oseen_term64(r, F, t);
+                    if (RPY) rpy_term64(r, F, v);
+                }
+                bad |= in && okq[q] && !self && r2 == 0.0;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    Tb[(a * TW + q) * RS] = t[a];
+                    if (RPY) Tb[((3 + a) * TW + q) * RS] = v[a];
+                }
+            }
+        }
+    };
+    /* The same terms by the shared short forms (rcp_sqrt_exact and the
+     * following), or form_plain where some lane's operands lie outside their
+     * range. MASK: the chunk holds one of the targets or ends past the
+     * system's last source; those terms get ir = 0, so they are +-0.0, and a
+     * sum that started at +0.0 does not change when either is added. */
+    auto form_any = [&](int k, double* Tb0, auto mask_c) {
+        constexpr bool MASK = decltype(mask_c)::value;
+        double rx[U][TW], ry[U][TW], rz[U][TW], r2[U][TW], fr[U][TW], ir[U][TW], iy[U][TW];
+        bool skip[U][TW];
+        Range64 rg;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int lj = k * CW + u * 64 + l;
+            const double Fx = s1[u].y, Fy = s2[u].x, Fz = s2[u].y;
 #pragma unroll
             for (int q = 0; q < TW; ++q) {
                 rx[u][q] = xi[q] - s0[u].x;
                 ry[u][q] = yi[q] - s0[u].y;
                 rz[u][q] = zi[q] - s1[u].x;
-                const double r2 = (rx[u][q] * rx[u][q] + ry[u][q] * ry[u][q]) + rz[u][q] * rz[u][q];
-                const bool self = j == iq[q];
-                skip[u][q] = !in || self || r2 == 0.0;
-                bad |= in && okq[q] && !self && r2 == 0.0;
-                r2s[u][q] = skip[u][q] ? 1.0 : r2;
-                safe &= f64_plain_range(r2s[u][q]);
+                r2[u][q] = (rx[u][q] * rx[u][q] + ry[u][q] * ry[u][q]) + rz[u][q] * rz[u][q];
+                if (MASK) {
+                    skip[u][q] = lj >= Nb || off + lj == iq[q];
+                    r2[u][q] = skip[u][q] ? 1.0 : r2[u][q];
+                }
+                fr[u][q] = (rx[u][q] * Fx + ry[u][q] * Fy) + rz[u][q] * Fz;
+                rg.r2(r2[u][q]);
+                rg.fr(fr[u][q]);
+                rcp_sqrt_exact(r2[u][q], ir[u][q], iy[u][q], rg.ones);
             }
         }
-        if (__all(safe)) {
+        bool ok = rg.ok();
+        if (__any(rg.small_fr())) { /* zero forces, as a rule */
+            asm volatile("" ::: "memory"); /* keeps the tests from being hoisted */
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int q = 0; q < TW; ++q) ir[u][q] = div_plain(1.0, sqrt_plain(r2s[u][q]));
-        } else {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int q = 0; q < TW; ++q) ir[u][q] = 1.0 / sqrt(r2s[u][q]);
+                for (int q = 0; q < TW; ++q) ok = ok && Range64::fr_fits(fr[u][q]);
+        }
+        if (__any(!ok)) {
+            form_plain(k, Tb0);
+            return;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -1925,20 +2105,27 @@ __global__ __launch_bounds__(64 * (NP + 1)) void k_pairs_f64w(Dev d, Epi e, int 
             const double Fx = s1[u].y, Fy = s2[u].x, Fz = s2[u].y;
 #pragma unroll
             for (int q = 0; q < TW; ++q) {
-                const double fr = (rx[u][q] * Fx + ry[u][q] * Fy) + rz[u][q] * Fz;
-                const double tt = fr / r2s[u][q];
-                Tb[(0 * TW + q) * RS] = skip[u][q] ? 0.0 : ir[u][q] * (Fx + tt * rx[u][q]);
-                Tb[(1 * TW + q) * RS] = skip[u][q] ? 0.0 : ir[u][q] * (Fy + tt * ry[u][q]);
-                Tb[(2 * TW + q) * RS] = skip[u][q] ? 0.0 : ir[u][q] * (Fz + tt * rz[u][q]);
+                const double tt = div_exact(fr[u][q], r2[u][q], iy[u][q]);
+                const double iv = MASK && skip[u][q] ? 0.0 : ir[u][q];
+                Tb[(0 * TW + q) * RS] = iv * (Fx + tt * rx[u][q]);
+                Tb[(1 * TW + q) * RS] = iv * (Fy + tt * ry[u][q]);
+                Tb[(2 * TW + q) * RS] = iv * (Fz + tt * rz[u][q]);
                 if (RPY) {
-                    const double ir3 = ir[u][q] / r2s[u][q];
+                    const double ir3 = div_exact(iv, r2[u][q], iy[u][q]);
                     const double t3 = 3.0 * tt;
-                    Tb[(3 * TW + q) * RS] = skip[u][q] ? 0.0 : ir3 * (Fx - t3 * rx[u][q]);
-                    Tb[(4 * TW + q) * RS] = skip[u][q] ? 0.0 : ir3 * (Fy - t3 * ry[u][q]);
-                    Tb[(5 * TW + q) * RS] = skip[u][q] ? 0.0 : ir3 * (Fz - t3 * rz[u][q]);
+                    Tb[(3 * TW + q) * RS] = ir3 * (Fx - t3 * rx[u][q]);
+                    Tb[(4 * TW + q) * RS] = ir3 * (Fy - t3 * ry[u][q]);
+                    Tb[(5 * TW + q) * RS] = ir3 * (Fz - t3 * rz[u][q]);
                 }
             }
         }
+    };
+    const int own = it.i0 - off; /* local index of the first target */
+    auto form = [&](int k, double* Tb0) {
+        if ((k * CW < own + TW && (k + 1) * CW > own) || (k + 1) * CW > Nb)
+            form_any(k, Tb0, std::integral_constant<bool, true>{});
+        else
+            form_any(k, Tb0, std::integral_constant<bool, false>{});
     };
     load(p);
     form(p, w_lds + p * BUF);
@@ -2629,11 +2816,10 @@ static hipError_t f64_ten(const Dev& d, const Epi& e, const Shape& sh, int mode,
     return sh.rpy ? go(k_pairs_f64<WG, IPL, 1>, WG, d, e, mode, s, tm) : go(k_pairs_f64<WG, IPL, 0>, WG, d, e, mode, s, tm);
 }
 
-template <int TW, int CW>
+template <int TW, int NP, int CW>
 static hipError_t go_f64w(const Dev& d, const Epi& e, const Shape& sh, int mode, hipStream_t s, const Timing& tm) {
-    constexpr int NP = F64W_NP;
     auto kern = sh.rpy ? k_pairs_f64w<TW, NP, CW, 1> : k_pairs_f64w<TW, NP, CW, 0>;
-    const size_t lds = f64w_lds_bytes(TW, sh.rpy, CW);
+    const size_t lds = f64w_lds_bytes({TW, NP, CW}, sh.rpy);
     const dim3 block(64 * (NP + 1));
     if (tm.start)
         hipExtLaunchKernelGGL(kern, dim3(d.nfitems), block, lds, s, tm.start, tm.stop, 0, d, e, mode);
@@ -2654,13 +2840,14 @@ hipError_t launch_pairs(const Dev& d, const Epi& e, const Shape& sh, int mode, h
         return hipErrorInvalidValue;
     }
     /* AD_FP64: the terms spread over waves (work list of target blocks) */
-    if (e.prec == PREC_FP64 && d.nfitems > 0 && sh.fused == 0) {
-        const int tw = f64w_targets(d.Ntot);
-        if (tw == 4)
-            return f64w_chunk(d.Ntot) == 128 ? go_f64w<4, 128>(d, e, sh, mode, s, tm)
-                                             : go_f64w<4, 64>(d, e, sh, mode, s, tm);
-        if (tw == 2) return go_f64w<2, 64>(d, e, sh, mode, s, tm);
-        return go_f64w<1, 64>(d, e, sh, mode, s, tm);
+    if (e.prec == PREC_FP64 && d.f64_blocks && d.nfitems > 0) {
+        const F64WShape f = f64w_shape(d.Ntot, sh.rpy);
+        if (f.tw == 4 && f.np == 2 && f.cw == 64) return go_f64w<4, 2, 64>(d, e, sh, mode, s, tm);
+        if (f.tw == 4 && f.np == 1 && f.cw == 64) return go_f64w<4, 1, 64>(d, e, sh, mode, s, tm);
+        if (f.tw == 4 && f.np == 1 && f.cw == 128 && !sh.rpy) return go_f64w<4, 1, 128>(d, e, sh, mode, s, tm);
+        if (f.tw == 2 && f.np == 2 && f.cw == 64) return go_f64w<2, 2, 64>(d, e, sh, mode, s, tm);
+        if (f.tw == 2 && f.np == 1 && f.cw == 128) return go_f64w<2, 1, 128>(d, e, sh, mode, s, tm);
+        return hipErrorInvalidValue;
     }
     /* FP64 kernels: 1 or 2 targets per lane, no j split inside a group; the
      * work list was built for this shape, so anything else is refused */
@@ -2865,6 +3052,7 @@ hipError_t launch_fused(const Dev& d, const Epi& e, const Shape& sh, int maxNb, 
 }
 
 hipError_t launch_epilogue(const Dev& d, const Epi& e, hipStream_t s) {
+    if (pairs_close(d, e)) return hipSuccess;
     hipLaunchKernelGGL(k_epilogue, blocks_for(d.Ntot, EPI_S), dim3(EPI_T), 0, s, d, e);
     return hipGetLastError();
 }

@@ -76,7 +76,7 @@ StaticLayout static_layout(int prec, int rpy, int N, const ad::PairShape& sh, bo
     L.sys_P = take(4);
     L.sys_pbase = take(8);
     L.items = take((size_t)L.nitems * sizeof(Item));
-    L.tw = ad::f64w_targets(N);
+    L.tw = ad::f64w_shape(N, rpy).tw;
     L.nfitems = prec == ad::PREC_FP64 && fp64_blocks ? (N + L.tw - 1) / L.tw : 0;
     L.fitems = take((size_t)L.nfitems * sizeof(Item));
     L.pA = take(f32 ? n * 16 : 0);
@@ -195,6 +195,7 @@ extern "C" int ad_mobility_apply_static(const ad_params* p, int32_t N, const dou
     d.items = reinterpret_cast<const Item*>(b + L.items);
     d.fitems = reinterpret_cast<const Item*>(b + L.fitems);
     d.nfitems = L.nfitems;
+    d.f64_blocks = L.nfitems > 0;
     if (prec == ad::PREC_FP32C) {
         d.pA = reinterpret_cast<float4*>(b + L.pA);
         d.pB = reinterpret_cast<float4*>(b + L.pB);

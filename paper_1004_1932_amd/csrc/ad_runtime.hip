@@ -348,7 +348,7 @@ static void build_items(ad_ctx* c) {
      * k_pairs_f64w) */
     c->fitems.clear();
     if (c->p.precision == AD_FP64 && L.fused == 0) {
-        const int tb = ad::f64w_targets(c->Ntot);
+        const int tb = ad::f64w_shape(c->Ntot, c->coef.rpy).tw;
         for (int b = 0; b < c->nsys; ++b) {
             const int Nb = 2 * c->S[b];
             for (int i = 0; i < Nb; i += tb) {
@@ -487,6 +487,7 @@ static void make_dev(ad_ctx* c) {
     d.H = c->nH ? reinterpret_cast<double*>(b + L.H) : nullptr;
     d.fitems = reinterpret_cast<const Item*>(b + L.fitems);
     d.nfitems = (int)c->fitems.size();
+    d.f64_blocks = c->p.precision == AD_FP64 && c->launch.fused == 0;
     d.items = reinterpret_cast<const Item*>(b + L.items);
     d.pA = reinterpret_cast<float4*>(b + L.pA);
     d.pB = reinterpret_cast<float4*>(b + L.pB);

@@ -1,0 +1,81 @@
+"""The FP64 pair sums at the edges of their forms: the short correctly rounded
+quotients and the plain expressions they give way to, the work-group shapes of
+AD_FP64, and AD_FP64_TILED's groups of targets and sources."""
+import numpy as np
+import pytest
+
+import paper_1004_1932_amd as P
+from workload import Params, make_single
+
+pytestmark = pytest.mark.gpu
+
+
+def _system(S, seed=0):
+    return make_single(S, 12.0 * S ** (1 / 3) + 20.0, seed).X
+
+
+@pytest.mark.parametrize("tensor", ["oseen", "rpy"])
+@pytest.mark.parametrize("S", [33, 64, 65, 768, 769, 1280, 1281, 1536, 1537])
+def test_fp64_product_block_shapes_bitwise(oracle, S, tensor):
+    """One dumbbell either side of the sizes where targets, producers and
+    chunk length change."""
+    X = _system(S)
+    F = np.random.default_rng(S).standard_normal(X.shape)
+    u = P.Simulator(Params(), [S], precision="fp64", tensor=tensor).mobility(X, F).cpu().numpy()
+    assert np.array_equal(u, oracle.mobility(Params(), X, F, int(tensor == "rpy")))
+
+
+@pytest.mark.parametrize("tensor", ["oseen", "rpy"])
+@pytest.mark.parametrize("case", ["zero forces", "one force", "tiny forces", "large forces", "all-ones", "scaled down",
+                                  "scaled up", "mixed"])
+def test_fp64_product_operand_ranges_bitwise(oracle, case, tensor):
+    """Operands in and out of the short forms' range: r2 beyond 2^+-400, r.F
+    beyond 2^+-500 and zero, distances whose square (or its root) has an
+    all-ones significand."""
+    S = 70
+    X = _system(S, 2)
+    F = np.random.default_rng(1).standard_normal(X.shape)
+    if case == "zero forces":
+        F[:] = 0.0
+    elif case == "one force":
+        F[:], F[3] = 0.0, [0.0, 1.0, 0.0]
+    elif case == "tiny forces":
+        F *= 1e-200
+    elif case == "large forces":
+        F *= 1e200
+    elif case == "all-ones":
+        one = np.nextafter(2.0, 0.0)                     # significand of ones
+        root = np.sqrt(np.nextafter(4.0, 0.0))           # its square rounds to all ones
+        X[:] = 0.0
+        X[:, 0] = 64.0 * np.arange(2 * S)
+        X[1::2, 0] = X[0::2, 0] + one
+        X[0], X[1], X[2] = [0, 0, 0], [one, 0, 0], [0, root, 0]
+    elif case == "scaled down":
+        X *= 2.0 ** -230
+    elif case == "scaled up":
+        X *= 2.0 ** 230
+    else:
+        F[::3] *= 1e-170
+        X[5] = X[4] + 2.0 ** -230
+    u = P.Simulator(Params(), [S], precision="fp64", tensor=tensor).mobility(X, F).cpu().numpy()
+    o = oracle.mobility(Params(), X, F, int(tensor == "rpy"), allow_nonfinite=True)
+    assert np.array_equal(u, o, equal_nan=True)
+
+
+@pytest.mark.parametrize("integrator", ["rk4", "heun"])
+@pytest.mark.parametrize("sizes", [[33], [800], [1300], [40, 1, 700, 65]])
+def test_fp64_stage_closed_by_the_pair_kernel_bitwise(oracle, sizes, integrator):
+    """The stage update, next forces and pack in the pair kernel's consumer
+    wave, replayed from graphs and launched directly."""
+    ens = [make_single(S, 12.0 * S ** (1 / 3) + 20.0, 7 + b) for b, S in enumerate(sizes)]
+    X, phi = np.concatenate([e.X for e in ens]), np.concatenate([e.phi for e in ens])
+    out = []
+    for graph in (False, True):
+        s = P.Simulator(Params(), sizes, precision="fp64", integrator=integrator, graph=graph)
+        s.set_state(X, phi)
+        for n in (1, 5, 17):
+            s.step(n)
+        out.append(s.get_state()[0].cpu().numpy())
+        assert s.check() == 0
+    Xo = oracle.run(Params(), X, phi, 23, S_per_sys=sizes, integrator=int(integrator == "heun"))[0]
+    assert np.array_equal(out[0], Xo) and np.array_equal(out[1], Xo)
