@@ -1751,8 +1751,8 @@ __device__ __forceinline__ double div_exact(double a, double x, double y) {
  *   t = fr/r2; acc = acc + ir*(F + t*r)
  * over every j != i of the chunk (partner included). A coincident pair is
  * skipped and raises the flag. With one chunk per system this is the
- * sequential FP64 sum exactly (AD_FP64 runs k_pairs_f64w, which gives the
- * same bits); AD_FP64_TILED runs several chunks. With RPY the correction (F - 3 t r) ir/r2 is
+ * sequential FP64 sum exactly: AD_FP64 where k_pairs_f64w, which gives the
+ * same bits, has no work list. With RPY the correction (F - 3 t r) ir/r2 is
  * summed in a second accumulator. */
 template <int WG, int IPL, int RPY>
 __global__ __launch_bounds__(WG) void k_pairs_f64(Dev d, Epi e, int mode) {
@@ -1849,6 +1849,167 @@ __global__ __launch_bounds__(WG) void k_pairs_f64(Dev d, Epi e, int mode) {
                 d.part[base + 5 * it.Nb + li] = bz[q];
             }
             if (bad) atomicOr(&d.ctl->flag, FLAG_NONFINITE);
+        }
+    }
+}
+
+/* AD_FP64_TILED: the sum over every j != i of the chunk (partner included) in
+ * FP64 with rsqrt64 and FMAs. A work-group of G waves takes 64 IPL targets of
+ * a work item (IPL per lane; an item of more targets is several work-groups)
+ * and stages tiles of 64 G sources through LDS; wave w sums the w-th 64 of
+ * every tile, F64_J sources at a time, and the waves' sums are added in wave
+ * order through LDS. A coincident pair is skipped and raises the flag. Sources
+ * whose r2 leaves the range of the short forms for some lane take the plain
+ * expressions. With RPY the correction is summed apart.
+ * What bounds it is FP64 issue: 23 instructions per term (31 with RPY) beside
+ * the range test, against about 60 (70) for the plain form's square root and
+ * divisions, which it replaced. A term's error does not grow: root mean
+ * square over random pairs, against 128 bits, 1.15e-16 (the FMA into the sum
+ * included) against 1.19e-16, and whole products at 100 to 3000 spheres lie
+ * 1 to 6 % nearer to 80-bit sums than the plain form's.
+ * The split by G waves is for balance and for small systems: one wave per 64
+ * targets summing whole chunks left 16 waves on the chip at 512 spheres.
+ * One product (pack, this, epilogue), us, against the plain form's: 512
+ * spheres 18.3 (60.2), 4096 31 (67), 16384 281 (667); RPY 18.8 (70), 41.5 (85),
+ * 357 (888). Two, eight and sixteen waves: 24, 18.3, 19 at 512, 289, 283, 314
+ * at 16384. */
+constexpr int F64_J = 4;
+
+template <int G, int IPL, int RPY>
+__global__ __launch_bounds__(64 * G) void k_pairs_f64t(Dev d, Epi e, int mode, int per_item) {
+    constexpr int TJ = 64 * G;
+    constexpr int NC = RPY ? 6 : 3;
+    union Lds {
+        double2 src[3][TJ];
+        double red[G > 1 ? G - 1 : 1][NC * IPL][64];
+    };
+    __shared__ Lds lds;
+    if (mode) advance_slots(d, e);
+    const Item it = d.items[blockIdx.x / per_item];
+    const int t = threadIdx.x, l = t & 63, w = t >> 6;
+    const int b0 = it.i0 + (int)(blockIdx.x % per_item) * 64 * IPL; /* first target of the group */
+    const int iend = it.i0 + it.ni;
+    if (b0 >= iend) return;
+    const int bend = min(iend, b0 + 64 * IPL);
+    const int ib = b0 + l * IPL;
+    double xi[IPL], yi[IPL], zi[IPL], acc[IPL][6];
+#pragma unroll
+    for (int q = 0; q < IPL; ++q) {
+        const int i = min(ib + q, bend - 1); /* lanes past the end repeat the last target, unused */
+        const double2 p0 = d.pD[3 * i], p1 = d.pD[3 * i + 1];
+        xi[q] = p0.x; yi[q] = p0.y; zi[q] = p1.x;
+#pragma unroll
+        for (int c = 0; c < 6; ++c) acc[q][c] = 0.0;
+    }
+    int bad = 0;
+    const int jend = it.j0 + it.nj;
+    for (int t0 = it.j0; t0 < jend; t0 += TJ) {
+        const int j = min(t0 + t, jend - 1);
+        const double2 a0 = d.pD[3 * j], a1 = d.pD[3 * j + 1], a2 = d.pD[3 * j + 2];
+        __syncthreads();
+        lds.src[0][t] = a0;
+        lds.src[1][t] = a1;
+        lds.src[2][t] = a2;
+        __syncthreads();
+        const int n = min(64, jend - t0 - 64 * w); /* this wave's sources of the tile */
+        auto plain = [&](int jj) {
+            const double2 c0 = lds.src[0][jj], c1 = lds.src[1][jj], c2 = lds.src[2][jj];
+            const double F[3] = {c1.y, c2.x, c2.y};
+#pragma unroll
+            for (int q = 0; q < IPL; ++q) {
+                const double r[3] = {xi[q] - c0.x, yi[q] - c0.y, zi[q] - c1.x};
+                const double r2 = (r[0] * r[0] + r[1] * r[1]) + r[2] * r[2];
+                if (t0 + jj == min(ib + q, bend - 1)) continue;
+                if (r2 == 0.0) {
+                    bad = 1;
+                    continue;
+                }
+                double o[3];
+                oseen_term64(r, F, o);
+                for (int c = 0; c < 3; ++c) acc[q][c] = acc[q][c] + o[c];
+                if (RPY) {
+                    rpy_term64(r, F, o);
+                    for (int c = 0; c < 3; ++c) acc[q][3 + c] = acc[q][3 + c] + o[c];
+                }
+            }
+        };
+        /* F64_J sources from jj; MASK: some of them may be the group's own
+         * targets, whose terms get r2 = 1 and no force */
+        auto group = [&](int jj, auto mask_c) {
+            constexpr bool MASK = decltype(mask_c)::value;
+            double rx[F64_J][IPL], ry[F64_J][IPL], rz[F64_J][IPL], r2[F64_J][IPL];
+            Range64 rg;
+#pragma unroll
+            for (int u = 0; u < F64_J; ++u)
+#pragma unroll
+                for (int q = 0; q < IPL; ++q) {
+                    rx[u][q] = xi[q] - lds.src[0][jj + u].x;
+                    ry[u][q] = yi[q] - lds.src[0][jj + u].y;
+                    rz[u][q] = zi[q] - lds.src[1][jj + u].x;
+                    r2[u][q] = __builtin_fma(rz[u][q], rz[u][q],
+                                             __builtin_fma(ry[u][q], ry[u][q], rx[u][q] * rx[u][q]));
+                    if (MASK && t0 + jj + u == min(ib + q, bend - 1)) r2[u][q] = 1.0;
+                    rg.r2(r2[u][q]);
+                }
+            if (!__all(rg.ok_r2())) {
+                for (int u = 0; u < F64_J; ++u) plain(jj + u);
+                return;
+            }
+#pragma unroll
+            for (int u = 0; u < F64_J; ++u) {
+                const double Gx = lds.src[1][jj + u].y, Gy = lds.src[2][jj + u].x, Gz = lds.src[2][jj + u].y;
+#pragma unroll
+                for (int q = 0; q < IPL; ++q) {
+                    const bool self = MASK && t0 + jj + u == min(ib + q, bend - 1);
+                    const double Fx = self ? 0.0 : Gx, Fy = self ? 0.0 : Gy, Fz = self ? 0.0 : Gz;
+                    const double ir = rsqrt64(r2[u][q]), ir2 = ir * ir;
+                    const double fr = __builtin_fma(rz[u][q], Fz, __builtin_fma(ry[u][q], Fy, rx[u][q] * Fx));
+                    const double tt = fr * ir2;
+                    acc[q][0] = __builtin_fma(ir, __builtin_fma(tt, rx[u][q], Fx), acc[q][0]);
+                    acc[q][1] = __builtin_fma(ir, __builtin_fma(tt, ry[u][q], Fy), acc[q][1]);
+                    acc[q][2] = __builtin_fma(ir, __builtin_fma(tt, rz[u][q], Fz), acc[q][2]);
+                    if (RPY) {
+                        const double ir3 = ir * ir2, t3 = -3.0 * tt;
+                        acc[q][3] = __builtin_fma(ir3, __builtin_fma(t3, rx[u][q], Fx), acc[q][3]);
+                        acc[q][4] = __builtin_fma(ir3, __builtin_fma(t3, ry[u][q], Fy), acc[q][4]);
+                        acc[q][5] = __builtin_fma(ir3, __builtin_fma(t3, rz[u][q], Fz), acc[q][5]);
+                    }
+                }
+            }
+        };
+        int jj = 64 * w;
+        const int je = jj + n;
+        if (t0 + je <= b0 || t0 + jj >= bend)
+            for (; jj + F64_J <= je; jj += F64_J) group(jj, std::integral_constant<bool, false>{});
+        else
+            for (; jj + F64_J <= je; jj += F64_J) group(jj, std::integral_constant<bool, true>{});
+        for (; jj < je; ++jj) plain(jj);
+    }
+    if (bad && ib < bend) atomicOr(&d.ctl->flag, FLAG_NONFINITE);
+    if (G > 1) {
+        __syncthreads(); /* the last tile is no longer read */
+        if (w > 0) {
+#pragma unroll
+            for (int q = 0; q < IPL; ++q)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) lds.red[w > 0 ? w - 1 : 0][q * NC + c][l] = acc[q][c];
+        }
+        __syncthreads();
+        if (w > 0) return;
+#pragma unroll
+        for (int g = 1; g < G; ++g)
+#pragma unroll
+            for (int q = 0; q < IPL; ++q)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) acc[q][c] = acc[q][c] + lds.red[g - 1][q * NC + c][l];
+    }
+    const long long base = d.sys_pbase[it.sys] + (long long)it.c * d.ncomp * it.Nb;
+#pragma unroll
+    for (int q = 0; q < IPL; ++q) {
+        const int li = ib + q - it.ioff;
+        if (ib + q < bend) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) d.part[base + (long long)c * it.Nb + li] = acc[q][c];
         }
     }
 }
@@ -2816,6 +2977,19 @@ static hipError_t f64_ten(const Dev& d, const Epi& e, const Shape& sh, int mode,
     return sh.rpy ? go(k_pairs_f64<WG, IPL, 1>, WG, d, e, mode, s, tm) : go(k_pairs_f64<WG, IPL, 0>, WG, d, e, mode, s, tm);
 }
 
+template <int IPL>
+static hipError_t go_f64t(const Dev& d, const Epi& e, const Shape& sh, int mode, hipStream_t s, const Timing& tm) {
+    constexpr int G = 4;
+    const int per_item = sh.wg / 64;
+    const dim3 grid(d.nitems * per_item), block(64 * G);
+    auto kern = sh.rpy ? k_pairs_f64t<G, IPL, 1> : k_pairs_f64t<G, IPL, 0>;
+    if (tm.start)
+        hipExtLaunchKernelGGL(kern, grid, block, 0, s, tm.start, tm.stop, 0, d, e, mode, per_item);
+    else
+        hipLaunchKernelGGL(kern, grid, block, 0, s, d, e, mode, per_item);
+    return hipGetLastError();
+}
+
 template <int TW, int NP, int CW>
 static hipError_t go_f64w(const Dev& d, const Epi& e, const Shape& sh, int mode, hipStream_t s, const Timing& tm) {
     auto kern = sh.rpy ? k_pairs_f64w<TW, NP, CW, 1> : k_pairs_f64w<TW, NP, CW, 0>;
@@ -2851,7 +3025,12 @@ hipError_t launch_pairs(const Dev& d, const Epi& e, const Shape& sh, int mode, h
     }
     /* FP64 kernels: 1 or 2 targets per lane, no j split inside a group; the
      * work list was built for this shape, so anything else is refused */
-    if (sh.wj != 1) return hipErrorInvalidValue;
+    if (sh.wj != 1 || (sh.wg != 64 && sh.wg != 256)) return hipErrorInvalidValue;
+    if (e.prec == PREC_FP64_TILED) {
+        if (sh.ipl == 1) return go_f64t<1>(d, e, sh, mode, s, tm);
+        if (sh.ipl == 2) return go_f64t<2>(d, e, sh, mode, s, tm);
+        return hipErrorInvalidValue;
+    }
     if (sh.wg == 64 && sh.ipl == 1) return f64_ten<64, 1>(d, e, sh, mode, s, tm);
     if (sh.wg == 64 && sh.ipl == 2) return f64_ten<64, 2>(d, e, sh, mode, s, tm);
     if (sh.wg == 256 && sh.ipl == 1) return f64_ten<256, 1>(d, e, sh, mode, s, tm);

@@ -79,3 +79,44 @@ def test_fp64_stage_closed_by_the_pair_kernel_bitwise(oracle, sizes, integrator)
         assert s.check() == 0
     Xo = oracle.run(Params(), X, phi, 23, S_per_sys=sizes, integrator=int(integrator == "heun"))[0]
     assert np.array_equal(out[0], Xo) and np.array_equal(out[1], Xo)
+
+
+@pytest.mark.parametrize("tensor", ["oseen", "rpy"])
+@pytest.mark.parametrize("launch", [None, dict(ipl=1, wg=64, jchunk=64), dict(ipl=2, wg=64, jchunk=100),
+                                    dict(ipl=2, wg=256, jchunk=300)])
+@pytest.mark.parametrize("sizes", [[1], [31], [32], [33], [127], [130], [257], [5, 66, 1, 129]])
+def test_fp64_tiled_groups_of_targets_and_sources(oracle, sizes, launch, tensor):
+    """Part-filled target groups, tiles and waves. 1e-13: sums of n terms,
+    each within a few ulp, in another order (n <= 514)."""
+    X = np.concatenate([_system(S, 3 + b) for b, S in enumerate(sizes)])
+    F = np.random.default_rng(9).standard_normal(X.shape)
+    s = P.Simulator(Params(), sizes, precision="fp64_tiled", launch=launch, tensor=tensor)
+    u = s.mobility(X, F).cpu().numpy()
+    off = np.concatenate([[0], np.cumsum(2 * np.asarray(sizes))])
+    for b in range(len(sizes)):
+        sl = slice(off[b], off[b + 1])
+        o = oracle.mobility(Params(), X[sl], F[sl], int(tensor == "rpy"))
+        assert np.linalg.norm(u[sl] - o) <= 1e-13 * np.linalg.norm(o), b
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -230, 1.0, 2.0 ** 230])
+def test_fp64_tiled_operand_ranges(oracle, scale):
+    X = _system(70, 2) * scale
+    F = np.random.default_rng(1).standard_normal(X.shape)
+    F[7] = 0.0
+    u = P.Simulator(Params(), [70], precision="fp64_tiled").mobility(X, F).cpu().numpy()
+    o = oracle.mobility(Params(), X, F)
+    assert np.linalg.norm(u - o) <= 1e-13 * np.linalg.norm(o)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp64_tiled"])
+def test_fp64_coincident_spheres_flagged_and_skipped(oracle, precision):
+    X = _system(90, 4)
+    X[101] = X[12]
+    F = np.random.default_rng(1).standard_normal(X.shape)
+    s = P.Simulator(Params(), [90], precision=precision)
+    s.set_state(X, np.zeros(90))
+    u = s.mobility(X, F).cpu().numpy()
+    assert s.check() == P.binding.AD_ENONFINITE
+    o = oracle.mobility(Params(), X, F, allow_nonfinite=True)
+    assert np.linalg.norm(u - o) <= 1e-13 * np.linalg.norm(o)
