@@ -102,9 +102,12 @@ typedef struct ad_params {
  * this size". A work-group of wg threads holds wg/64/wj waves on distinct
  * target spheres (ipl per lane) and wj waves that split every j-tile.
  * AD_FP64 with fused = 0 validates ipl, jchunk, wg and wj but its pair
- * kernel does not use them: a work-group of a producer and a consumer wave
- * per 1, 2 or 4 target spheres (about N_total / 1024), every source of the
- * system in ascending order. */
+ * kernel does not use them: a work-group of one or two producer waves and a
+ * consumer wave per 2 or 4 target spheres, every source of the system in
+ * ascending order. Nor do the steps of AD_FP32C with fused = 0 for one large
+ * system (from 9728 spheres with hi/lo positions, 16384 with single floats,
+ * 8192 with steric forces): their pair kernel forms every unordered pair once.
+ * ad_mobility_apply uses the shape in every case. */
 typedef struct ad_launch {
     int32_t ipl;      /* target spheres per lane: 1, 2 or 4 (FP64 modes: 1 or 2; dense: 1) */
     int32_t jchunk;   /* source spheres per work-group, >= 64 (AD_FP64: whole system;

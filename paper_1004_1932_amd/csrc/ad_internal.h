@@ -100,6 +100,10 @@ struct Dev {
                            resident form: one per system; AD_FP64 pair sum: target blocks */
     int nfitems;        /* 0: one system, blocks in order */
     int f64_blocks;     /* 1: fitems are the AD_FP64 pair sum's target blocks */
+    const Item* sym_items;     /* the symmetric pair sum's work list (ad_sym.hip), */
+    const long long* sym_base; /* [blocks] first partial of each block, */
+    const int* sym_P;          /* [blocks] its partial slots, */
+    int nsym, sym_bs;          /* items and spheres per block; 0: another pair kernel */
     const long long* sys_hbase; /* [nsys] dense mode: first element of the system's tensor */
     const double* tab;  /* [ring][8] (sin, cos) of omega*t per epilogue stage */
     int ring;           /* entries in tab, a power of two (rows are step & (ring - 1)) */
@@ -205,6 +209,27 @@ hipError_t launch_forces(const Dev& d, const Coef& c, const double* Xaos, double
  * the dispatch itself. */
 hipError_t launch_pairs(const Dev& d, const Epi& e, const Shape& sh, int mode, hipStream_t s,
                         hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+/* FP32C stage of one large system, every unordered pair once (ad_sym.hip);
+ * the epilogue follows */
+hipError_t launch_pairs_sym(const Dev& d, const Epi& e, const Shape& sh, hipStream_t s,
+                            hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+/* The systems it takes. It saves instructions, most with hi/lo positions and
+ * with steric forces (whose other kernel tests every pair's distance), and
+ * pays for partial sums at both ends of a pair. us per RK4 step against the
+ * ordered pair kernel: hi/lo 9000 spheres 245 (237), 10000 290 (297), 12000
+ * 362 (377), 20000 844 (965), 65536 6.9 ms (9.15); single-float 15002 407
+ * (408), 17000 537 (571), 32768 1710 (1967); steric 8300 225 (277), 15002 460
+ * (586), 65536 7.1 ms (9.0). */
+inline bool sym_takes(int N, int hilo, int steric) {
+    return N >= (steric ? 8192 : hilo ? 9728 : 16384);
+}
+/* spheres per block: work-groups of 4 or 8 waves, 128 spheres per wave (the
+ * larger block halves the partial sums of the largest systems) */
+__host__ __device__ inline int sym_block(int N) { return N >= 32768 ? 1024 : 512; }
+/* the work items aimed at: 1024 to 8192 differ by up to 7 %, the best one
+ * changing with how the runs divide (15002 spheres: 540, 500, 498, 515, 506 us
+ * at 1024, 2048, 3072, 4096, 8192) */
+constexpr int SYM_ITEMS = 3072;
 /* dense mode (ad_dense.hip): assemble every system's pair tensor from the
  * FP64 pack, then multiply it by the packed forces into the partial sums;
  * the events, if given, bracket both launches */

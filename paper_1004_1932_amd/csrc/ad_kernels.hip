@@ -448,9 +448,15 @@ __device__ void epi_block(const Dev& d, const Epi& e, int i0, int ni, long long 
         const int b = d.dsys[i >> 1];
         const int off = d.sys_off[b];
         const int Nb = d.sys_off[b + 1] - off;
-        const int P = d.sys_P[b];
-        const long long stride = (long long)d.ncomp * Nb;
+        int P = d.sys_P[b];
+        long long stride = (long long)d.ncomp * Nb;
         const double* p = d.part + d.sys_pbase[b] + (long long)a * Nb + (i - off);
+        if (d.nsym && !apply) { /* the symmetric pair sum's slots of the sphere's block */
+            const int bs = d.sym_bs, B = i / bs;
+            P = d.sym_P[B];
+            stride = 3LL * bs;
+            p = d.part + d.sym_base[B] + (long long)a * bs + (i - B * bs);
+        }
         const int o = a * N + i;
         /* independent loads first, so they are in flight together */
         const double u0 = d.U0[o];

@@ -59,6 +59,10 @@ struct ad_ctx {
     long long npart = 0;
     std::vector<long long> hbase; /* dense mode: first tensor element per system */
     std::vector<Item> fitems;     /* fused stages of an ensemble: (system, target block) */
+    std::vector<Item> sitems;     /* symmetric pair sum: (block, run of chunks) */
+    std::vector<long long> sbase; /* and per block its first partial */
+    std::vector<int32_t> sP;      /* and number of partial slots */
+    long long nspart = 0;         /* its partials in all */
     bool fused_ready = false;     /* the fused kernels may use all of LDS */
     long long nH = 0;             /* dense mode: tensor elements over all systems */
     int maxNb = 0;
@@ -304,8 +308,45 @@ static void build_dense_items(ad_ctx* c) {
     });
 }
 
+/* Work list of the symmetric pair sum (ad_sym.hip): FP32C stages of one system
+ * in two kernels, where sym_takes. Block I takes the chunks of 64
+ * spheres from its own first one to the end, in runs of about the length that
+ * makes SYM_ITEMS items. A block's partial slots: one per lower block, then
+ * one per run of its own. */
+static void build_sym_items(ad_ctx* c) {
+    c->sitems.clear();
+    c->sbase.clear();
+    c->sP.clear();
+    c->nspart = 0;
+    if (c->p.precision != AD_FP32C || c->nsys != 1 || c->launch.fused != 0 ||
+        !ad::sym_takes(c->Ntot, c->launch.posmode == AD_POS_HILO, c->p.steric_k != 0.0))
+        return;
+    const int N = c->Ntot, bs = ad::sym_block(N), nb = (N + bs - 1) / bs, nch = (N + 63) / 64, cpb = bs / 64;
+    long long units = 0;
+    for (int b = 0; b < nb; ++b) units += nch - b * cpb;
+    const int run = (int)std::max<long long>(1, (units + ad::SYM_ITEMS - 1) / ad::SYM_ITEMS);
+    for (int b = 0; b < nb; ++b) {
+        int slot = b;
+        for (int j = b * cpb; j < nch; j += run) {
+            Item it{};
+            it.i0 = b * bs;
+            it.ni = std::min(bs, N - b * bs);
+            it.j0 = j;
+            it.nj = std::min(run, nch - j);
+            it.c = slot++;
+            it.Nb = N;
+            c->sitems.push_back(it);
+        }
+        c->sbase.push_back(c->nspart);
+        c->sP.push_back(slot);
+        c->nspart += 3LL * bs * slot;
+    }
+    std::stable_sort(c->sitems.begin(), c->sitems.end(), [](const Item& a, const Item& b) { return a.nj > b.nj; });
+}
+
 static void build_items(ad_ctx* c) {
     const ad_launch& L = c->launch;
+    build_sym_items(c);
     const int NC = ncomp_of(c);
     if (is_dense(c)) {
         build_dense_items(c);
@@ -410,7 +451,7 @@ static void build_items(ad_ctx* c) {
 
 struct Layout {
     size_t ctl, X, R, U0, Y, Fs, nbr_cnt, nbr_idx, phitrig, dsys, sys_off, sys_P, sys_pbase, sys_hbase, items,
-        pA, pB, pC, pD, pA2, pB2, pC2, pD2, part, tab, H, fitems, total;
+        pA, pB, pC, pD, pA2, pB2, pC2, pD2, part, tab, H, fitems, sitems, sbase, sP, total;
 };
 
 static Layout layout(const ad_ctx* c) {
@@ -447,10 +488,13 @@ static Layout layout(const ad_ctx* c) {
     L.pB2 = take(f32 ? N * 16 : 0);
     L.pC2 = take(f32 ? N * 8 : 0);
     L.pD2 = take(f32 ? 0 : 3 * N * 16);
-    L.part = take((size_t)c->npart * 8);
+    L.part = take((size_t)std::max(c->npart, c->nspart) * 8);
     L.tab = take((size_t)kRing * 8 * 8);
     L.H = take((size_t)c->nH * 8);
     L.fitems = take(c->fitems.size() * sizeof(Item));
+    L.sitems = take(c->sitems.size() * sizeof(Item));
+    L.sbase = take(c->sbase.size() * 8);
+    L.sP = take(c->sP.size() * 4);
     L.total = o;
     return L;
 }
@@ -488,6 +532,11 @@ static void make_dev(ad_ctx* c) {
     d.fitems = reinterpret_cast<const Item*>(b + L.fitems);
     d.nfitems = (int)c->fitems.size();
     d.f64_blocks = c->p.precision == AD_FP64 && c->launch.fused == 0;
+    d.sym_items = reinterpret_cast<const Item*>(b + L.sitems);
+    d.sym_base = reinterpret_cast<const long long*>(b + L.sbase);
+    d.sym_P = reinterpret_cast<const int*>(b + L.sP);
+    d.nsym = (int)c->sitems.size();
+    d.sym_bs = c->sitems.empty() ? 0 : ad::sym_block(c->Ntot);
     d.items = reinterpret_cast<const Item*>(b + L.items);
     d.pA = reinterpret_cast<float4*>(b + L.pA);
     d.pB = reinterpret_cast<float4*>(b + L.pB);
@@ -540,6 +589,11 @@ static int upload_tables(ad_ctx* c) {
     if (!c->fitems.empty())
         HIPCHECK(c, hipMemcpy(b + L.fitems, c->fitems.data(), c->fitems.size() * sizeof(Item),
                               hipMemcpyHostToDevice));
+    if (!c->sitems.empty()) {
+        HIPCHECK(c, hipMemcpy(b + L.sitems, c->sitems.data(), c->sitems.size() * sizeof(Item), hipMemcpyHostToDevice));
+        HIPCHECK(c, hipMemcpy(b + L.sbase, c->sbase.data(), c->sbase.size() * 8, hipMemcpyHostToDevice));
+        HIPCHECK(c, hipMemcpy(b + L.sP, c->sP.data(), c->sP.size() * 4, hipMemcpyHostToDevice));
+    }
     return AD_OK;
 }
 
@@ -636,6 +690,8 @@ static int launch_pairs_timed(ad_ctx* c, const Dev& d, const ad::Epi& e, int mod
         }
         if (is_dense(c))
             HIPCHECK(c, ad::launch_dense(d, e, mode, c->maxNb, st));
+        else if (mode == 1 && d.nsym)
+            HIPCHECK(c, ad::launch_pairs_sym(d, e, sh, st));
         else
             HIPCHECK(c, ad::launch_pairs(d, e, sh, mode, st));
         return AD_OK;
@@ -652,6 +708,8 @@ static int launch_pairs_timed(ad_ctx* c, const Dev& d, const ad::Epi& e, int mod
         HIPCHECK(c, ad::launch_fused(d, e, sh, c->maxNb, st, c->ev[2 * c->ev_used], c->ev[2 * c->ev_used + 1]));
     else if (is_dense(c))
         HIPCHECK(c, ad::launch_dense(d, e, mode, c->maxNb, st, c->ev[2 * c->ev_used], c->ev[2 * c->ev_used + 1]));
+    else if (mode == 1 && d.nsym)
+        HIPCHECK(c, ad::launch_pairs_sym(d, e, sh, st, c->ev[2 * c->ev_used], c->ev[2 * c->ev_used + 1]));
     else
         HIPCHECK(c, ad::launch_pairs(d, e, sh, mode, st, c->ev[2 * c->ev_used], c->ev[2 * c->ev_used + 1]));
     c->ev_used += 1;
