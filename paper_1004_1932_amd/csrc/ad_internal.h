@@ -144,6 +144,14 @@ __device__ __forceinline__ void advance_slots(const Dev& d, const Epi& e) {
     d.ctl->trig[e.stage][1] = d.tab[row * 8 + 2 * e.stage + 1];
 }
 
+/* The slots alone, for the kernels that close their stage themselves and read
+ * the step table directly (step: the index the caller has read). */
+__device__ __forceinline__ void advance_step(const Dev& d, const Epi& e, long long step) {
+    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+    if (e.stage == 0) d.ctl->slot[1] = step;
+    if (e.stage == e.nst - 1) d.ctl->slot[0] = step + 1;
+}
+
 /* Launch shape of the pair kernel: WG threads = (WG/64/wj) waves on distinct
  * targets x wj waves splitting each j-tile; ipl targets per lane; split = 1
  * for hi/lo positions (FP32C only). One work item covers 64*ipl*WG/64/wj
@@ -292,15 +300,14 @@ __host__ __device__ inline int f64w_lds_bytes(const F64WShape& f, int rpy) {
 /* the most target spheres per work-group of the streamed fused stage */
 constexpr int FT_I = 16;
 /* target spheres per work-group of the streamed fused stage for Ntot
- * spheres in all: 4, 8 or 16, about Ntot / 256, so that the launch holds
- * about one work-group per compute unit (every work-group reads every source
- * of its system: two on a compute unit double that traffic; fewer than 256
- * leave compute units idle) */
-__host__ __device__ inline int stream_targets(int Ntot) {
-    int ti = 4;
-    while (ti < FT_I && 2 * 256 * ti <= Ntot) ti *= 2;
-    return ti;
-}
+ * spheres in all: about one work-group per compute unit (every work-group
+ * reads every source of its system and has the same fixed cost: two on a
+ * compute unit take nearly twice as long, fewer than 256 leave compute units
+ * idle). 4 up to 256 work-groups, then 8 up to 512 of them (from 2048 spheres
+ * two share a compute unit; 16 targets left fewer still), then 16. us per RK4
+ * step with 4 and 8 targets: 1040 spheres 24.3, 22.5; 1354 26.2, 23.2; 1900
+ * 28.7, 25.5; with 8 and 16: 2048 25.6, 31.0; 4096 57, 46.7. */
+__host__ __device__ inline int stream_targets(int Ntot) { return Ntot <= 1024 ? 4 : Ntot < 4096 ? 8 : FT_I; }
 /* waves per work-group of the streamed fused stage with ti targets: 16 with
  * 16 targets, else 8. With 4 targets (the small systems) the few sources per
  * lane make the combination of 16 waves' sums a large share; with 8 targets

@@ -121,6 +121,17 @@ __device__ __forceinline__ void two_sum_acc(float& hi, float& lo, float v) {
 }
 
 
+/* 1/sqrt(r2) from v_rsq_f64 (about 2^-24) and one third-order step
+ * y (1 + e/2 + 3 e^2/8), e = 1 - r2 y^2: within an ulp. (One Newton step, two
+ * instructions fewer, leaves 4e-15.) */
+__device__ __forceinline__ double rsqrt64(double r2) {
+    const double y = __builtin_amdgcn_rsq(r2);
+    const double g = r2 * y;
+    const double e = __builtin_fma(-g, y, 1.0);
+    const double p = __builtin_fma(e, 0.375, 0.5);
+    return __builtin_fma(y * e, p, y);
+}
+
 /* Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of two
  * 32x32->64 multiplications by the published multipliers, the key bumped by
  * the Weyl constants between rounds. */
@@ -140,18 +151,88 @@ __device__ __forceinline__ void philox4x32_10(unsigned c[4], unsigned k0, unsign
     }
 }
 
+/* log u for u in (0, 1), within two ulp: u = 2^e m, m in [sqrt(1/2), sqrt(2)),
+ * log m = 2 atanh(q), q = (m - 1)/(m + 1), by the series of atanh up to q^23
+ * (|q| < 0.172: the next term is below 2^-63). */
+__device__ __forceinline__ double log_unit(double u) {
+    double m = __builtin_amdgcn_frexp_mant(u); /* in [1/2, 1) */
+    int e = __builtin_amdgcn_frexp_exp(u);
+    const bool low = m < 0.70710678118654757;
+    m = low ? m + m : m;
+    e = low ? e - 1 : e;
+    const double f = m - 1.0, g = m + 1.0;
+    double y = __builtin_amdgcn_rcp(g);
+    y = __builtin_fma(y, __builtin_fma(-g, y, 1.0), y);
+    double q = f * y;
+    q = __builtin_fma(__builtin_fma(-g, q, f), y, q);
+    const double z = q * q;
+    double p = 1.0 / 23.0;
+    p = __builtin_fma(p, z, 1.0 / 21.0);
+    p = __builtin_fma(p, z, 1.0 / 19.0);
+    p = __builtin_fma(p, z, 1.0 / 17.0);
+    p = __builtin_fma(p, z, 1.0 / 15.0);
+    p = __builtin_fma(p, z, 1.0 / 13.0);
+    p = __builtin_fma(p, z, 1.0 / 11.0);
+    p = __builtin_fma(p, z, 1.0 / 9.0);
+    p = __builtin_fma(p, z, 1.0 / 7.0);
+    p = __builtin_fma(p, z, 1.0 / 5.0);
+    p = __builtin_fma(p, z, 1.0 / 3.0);
+    const double q2 = q + q;
+    /* e log 2 in two parts: the first product is exact (log 2 to 36 bits) */
+    const double lo = __builtin_fma((double)e, 0x1.cf79abc9e3b3ap-40, (q2 * z) * p);
+    return __builtin_fma((double)e, 0x1.62e42fefa0000p-1, q2 + lo);
+}
+
+/* sin (a = 1) or cos of 2 pi u, u in (0, 1) a multiple of 2^-33: the turn is
+ * reduced exactly by quarters to |t| <= 1/8, then Taylor polynomials of
+ * 2 pi t (the next terms are below 2^-57). */
+__device__ __forceinline__ double trig_turn(double u, int a) {
+    const double k = __builtin_rint(4.0 * u);
+    const double x = (u - 0.25 * k) * 6.283185307179586477;
+    const double z = x * x;
+    double s = 1.0 / 355687428096000.0;
+    s = __builtin_fma(s, z, -1.0 / 1307674368000.0);
+    s = __builtin_fma(s, z, 1.0 / 6227020800.0);
+    s = __builtin_fma(s, z, -1.0 / 39916800.0);
+    s = __builtin_fma(s, z, 1.0 / 362880.0);
+    s = __builtin_fma(s, z, -1.0 / 5040.0);
+    s = __builtin_fma(s, z, 1.0 / 120.0);
+    s = __builtin_fma(s, z, -1.0 / 6.0);
+    s = __builtin_fma(x * z, s, x);
+    double c = 1.0 / 20922789888000.0;
+    c = __builtin_fma(c, z, -1.0 / 87178291200.0);
+    c = __builtin_fma(c, z, 1.0 / 479001600.0);
+    c = __builtin_fma(c, z, -1.0 / 3628800.0);
+    c = __builtin_fma(c, z, 1.0 / 40320.0);
+    c = __builtin_fma(c, z, -1.0 / 720.0);
+    c = __builtin_fma(c, z, 1.0 / 24.0);
+    c = __builtin_fma(c, z, -0.5);
+    c = __builtin_fma(c, z, 1.0);
+    /* cos is sin a quarter turn on */
+    const int n = (int)k + (a == 1 ? 0 : 1);
+    const double v = (n & 1) ? c : s;
+    const unsigned long long sign = (unsigned long long)((n >> 1) & 1) << 63;
+    return __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, v) ^ sign);
+}
+
 /* Standard normal component a (0..2) of sphere i at step n: Box-Muller on
  * the four uniforms (x + 1/2) 2^-32 of one Philox block with counter
- * (i, n) and key seed. */
-__device__ double gauss_component(unsigned long long seed, int i, long long n, int a) {
+ * (i, n) and key seed. (With the library's log, sin and cos, made for any
+ * operand, the 1354-sphere Heun step with noise took 3.5 us more.) */
+__device__ __forceinline__ double gauss_component(unsigned long long seed, int i, long long n, int a) {
     unsigned c[4] = {(unsigned)i, (unsigned)n, (unsigned)((unsigned long long)n >> 32), 0u};
     philox4x32_10(c, (unsigned)seed, (unsigned)(seed >> 32));
-    const double two_pi = 2.0 * 3.14159265358979323846;
-    const int pr = (a == 2) ? 2 : 0;
-    const double u0 = ((double)c[pr] + 0.5) / 4294967296.0;
-    const double u1 = ((double)c[pr + 1] + 0.5) / 4294967296.0;
-    const double rr = sqrt(-2.0 * log(u0));
-    return (a == 1) ? rr * sin(two_pi * u1) : rr * cos(two_pi * u1);
+    const double u0 = ((double)(a == 2 ? c[2] : c[0]) + 0.5) * 0x1p-32;
+    const double u1 = ((double)(a == 2 ? c[3] : c[1]) + 0.5) * 0x1p-32;
+    const double x = -2.0 * log_unit(u0); /* in [2^-32, 46] */
+    double y = rsqrt64(x), r = x * y;
+    r = __builtin_fma(__builtin_fma(-r, r, x), 0.5 * y, r);
+    return r * trig_turn(u1, a);
+}
+
+/* The noise of component a of sphere i in both stages of Heun step n. */
+__device__ __forceinline__ double stage_noise(const Coef& c, int i, long long n, int a) {
+    return c.noise ? c.g * gauss_component(c.seed, i, n, a) : 0.0;
 }
 
 /* Write the pair-kernel pack and the self (+partner) velocity u0 of the two
@@ -183,8 +264,9 @@ __device__ __forceinline__ void store_pack_sphere(const Dev& d, const Coef& c, i
 }
 
 /* The closing update of the FP32C stage kernels uses these two forms of
- * spring_forces and store_pack_sphere: one rsqrt (a few ulp) in place of
- * each IEEE sqrt and division. In the FP32C path the state stays FP64 and
+ * spring_forces and store_pack_sphere: one rsqrt64 (within an ulp) in place
+ * of the IEEE square roots and divisions; r = y - yp is +-(y1 - y0) exactly,
+ * so the partner term takes the spring's 1/d. In the FP32C path the state stays FP64 and
  * only the pair sums are FP32, so a relative error near 1e-16 here is far
  * below theirs (about 1e-7); the FP64 paths keep the IEEE forms, whose
  * operation order the bitwise parity with the plain sum depends on. With
@@ -195,7 +277,7 @@ __device__ __forceinline__ double spring_forces_rs(const Coef& c, const double y
                                                    double f0[3], double f1[3]) {
     /* -k (d - L) n / d = k (L / d - 1) n */
     const double nx = y1[0] - y0[0], ny = y1[1] - y0[1], nz = y1[2] - y0[2];
-    const double id = rsqrt((nx * nx + ny * ny) + nz * nz);
+    const double id = rsqrt64((nx * nx + ny * ny) + nz * nz);
     const double L = c.ell + c.lam * (st * cphi + ct * sphi);
     const double cc = c.k * (L * id - 1.0);
     f1[0] = cc * nx;
@@ -209,10 +291,10 @@ __device__ __forceinline__ double spring_forces_rs(const Coef& c, const double y
 
 template <int SPLIT>
 __device__ __forceinline__ void store_pack_sphere_rs(const Dev& d, const Coef& c, int i, const double y[3],
-                                                     const double yp[3], const double f[3], const double fp[3]) {
+                                                     const double yp[3], const double f[3], const double fp[3],
+                                                     double ir) {
     const int N = d.Ntot;
     const double r[3] = {y[0] - yp[0], y[1] - yp[1], y[2] - yp[2]};
-    const double ir = rsqrt((r[0] * r[0] + r[1] * r[1]) + r[2] * r[2]);
     const double ir2 = ir * ir;
     const double t = ((r[0] * fp[0] + r[1] * fp[1]) + r[2] * fp[2]) * ir2;
     for (int a = 0; a < 3; ++a) {
@@ -372,12 +454,13 @@ __global__ void k_forces(Dev d, Coef c, const double* __restrict__ Xa, double st
 
 /* ------------------------------------------------------------ epilogue */
 
-/* Stage update of one state component o = a N + i from its velocity k:
+/* Stage update of one state component o = a N + i from its velocity k (and
+ * the step's noise nz):
  * RK4 keeps the weighted sum of the stage velocities in R and writes X at the
  * last stage; Heun adds the same noise in both stages. Returns the position
  * at which the next stage evaluates the velocity. */
-__device__ __forceinline__ double stage_update(const Dev& d, const Epi& e, int o, int i, int a, double k,
-                                               double x, double r, long long step) {
+__device__ __forceinline__ double stage_update(const Dev& d, const Epi& e, int o, double k,
+                                               double x, double r, double nz) {
     const Coef& c = e.c;
     const int stage = e.stage;
     double y;
@@ -396,7 +479,6 @@ __device__ __forceinline__ double stage_update(const Dev& d, const Epi& e, int o
             d.X[o] = y;
         }
     } else { /* Heun, with the same noise in both stages */
-        const double nz = c.noise ? c.g * gauss_component(c.seed, i, step, a) : 0.0;
         if (stage == 0) {
             d.R[o] = k;
             y = x + c.dt * k;
@@ -491,7 +573,7 @@ __device__ void epi_block(const Dev& d, const Epi& e, int i0, int ni, long long 
             e.u_aos[3 * i + a] = k;
             continue;
         }
-        const double y = stage_update(d, e, o, i, a, k, x, r, step);
+        const double y = stage_update(d, e, o, k, x, r, apply ? 0.0 : stage_noise(c, i, step, a));
         ys[sl][a] = y;
         const double dd = y - yold;
         mv[sl][a] = dd * dd;
@@ -790,6 +872,53 @@ __global__ __launch_bounds__(WG) void k_pairs_f32c(Dev d, Epi e, int mode) {
     }
 }
 
+/* (hi, lo) += (oh, ol) with TwoSum; the same bits whichever is added to which */
+__device__ __forceinline__ void add_hilo(float& hi, float& lo, float oh, float ol) {
+    const float s = hi + oh;
+    const float bb = s - hi;
+    const float err = (hi - (s - bb)) + (oh - bb);
+    hi = s;
+    lo = (lo + ol) + err;
+}
+
+/* The sums v = (hi.x, lo.x, hi.y, lo.y, hi.z, lo.z) of the lanes that agree
+ * modulo TI (4, 8 or 16), added up; every lane ends with the total of its
+ * class. Distances 8 and 4 by DPP rotations of a row (after the first, rows
+ * repeat every 8 lanes, so a rotation by 4 is an exchange at distance 4), 16
+ * and 32 by row and half-wave swaps, all VALU operations: no LDS round trip
+ * per level. */
+template <int TI>
+__device__ __forceinline__ void wave_add_hilo(float v[6]) {
+    auto ror = [&](auto ctrl) {
+        float o[6];
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+            o[q] = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v[q]),
+                                                                      decltype(ctrl)::value, 0xF, 0xF, true));
+#pragma unroll
+        for (int a = 0; a < 3; ++a) add_hilo(v[2 * a], v[2 * a + 1], o[2 * a], o[2 * a + 1]);
+    };
+    if (TI <= 8) ror(std::integral_constant<int, 0x128>{}); /* row_ror:8 */
+    if (TI <= 4) ror(std::integral_constant<int, 0x124>{}); /* row_ror:4 */
+    auto swap = [&](auto rows) {
+        float o[6];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            const unsigned x = __builtin_bit_cast(unsigned, v[q]);
+            const auto r = decltype(rows)::value == 16 ? __builtin_amdgcn_permlane16_swap(x, x, false, false)
+                                                       : __builtin_amdgcn_permlane32_swap(x, x, false, false);
+            /* (a bit cast of the vector's element itself takes element 0) */
+            const unsigned r0 = r[0], r1 = r[1];
+            v[q] = __builtin_bit_cast(float, r0);
+            o[q] = __builtin_bit_cast(float, r1);
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) add_hilo(v[2 * a], v[2 * a + 1], o[2 * a], o[2 * a + 1]);
+    };
+    swap(std::integral_constant<int, 16>{});
+    swap(std::integral_constant<int, 32>{});
+}
+
 /* ------------------------------------------------------- fused stage */
 
 /* One stage in one kernel. A work-group of NW waves owns FS_I = 16 target
@@ -905,18 +1034,21 @@ __global__ __launch_bounds__(64 * NW) void k_stage_fused(Dev d, Epi e) {
     }
     const int di = (i - off) >> 1; /* local dumbbell (off is even) */
     __syncthreads();
-    /* after the staging barrier, so that their dependent loads stall only
-     * wave 0, whose sums are not the last to finish: the step slots for the
-     * next kernel, and for lane q < ni the phase of dumbbell q/2 and the
-     * (sin, cos)(omega t) of this stage */
-    advance_slots(d, e);
-    double st = 0.0, ct = 0.0;
+    /* after the staging barrier, in flight under the sums: the step slots for
+     * the next kernel, for lane q < ni the phase of dumbbell q/2 and the
+     * (sin, cos)(omega t) of this stage, and the noise of the lane's component */
+    advance_step(d, e, step);
+    double st = 0.0, ct = 0.0, nz = 0.0;
     double2 tp = make_double2(0.0, 0.0);
     if (tid < ni) {
         const long long row = step & (d.ring - 1);
         st = d.tab[row * 8 + 2 * e.stage];
         ct = d.tab[row * 8 + 2 * e.stage + 1];
         tp = d.phitrig[(i0 >> 1) + (tid >> 1)];
+    }
+    if (e.c.noise && tid < 3 * ni) {
+        nz = stage_noise(e.c, i0 + tid / 3, step, tid % 3);
+        asm volatile("" : "+v"(nz)); /* formed here, not where the update needs it */
     }
 
     const float crr = e.c.crr;
@@ -974,28 +1106,14 @@ __global__ __launch_bounds__(64 * NW) void k_stage_fused(Dev d, Epi e) {
     /* combine the JS partial sums of each target in a fixed order: the four
      * quarters of a wave by shuffles (both partners get the same sum), then
      * the NW waves through LDS in a pairwise tree */
-    auto combine = [](float& hi, float& lo, float oh, float ol) {
-        const float s = hi + oh;
-        const float bb = s - hi;
-        const float err = (hi - (s - bb)) + (oh - bb);
-        hi = s;
-        lo = (lo + ol) + err;
-    };
-#pragma unroll
-    for (int sh = 16; sh <= 32; sh *= 2) {
-        const float oax = __shfl_xor(ax, sh), obx = __shfl_xor(bx, sh);
-        const float oay = __shfl_xor(ay, sh), oby = __shfl_xor(by, sh);
-        const float oaz = __shfl_xor(az, sh), obz = __shfl_xor(bz, sh);
-        combine(ax, bx, oax, obx);
-        combine(ay, by, oay, oby);
-        combine(az, bz, oaz, obz);
-    }
+    float v[6] = {ax, bx, ay, by, az, bz};
+    wave_add_hilo<16>(v);
     __syncthreads(); /* the sources are no longer read */
     float* red = reinterpret_cast<float*>(fs_lds);                  /* [NW waves][FS_I][6] */
     double* ys = reinterpret_cast<double*>(fs_lds) + NW * FS_I * 3; /* [FS_I][3] stage positions */
     if (g == 0) {
         float* r = red + (w * FS_I + t) * 6;
-        r[0] = ax; r[1] = bx; r[2] = ay; r[3] = by; r[4] = az; r[5] = bz;
+        for (int q = 0; q < 6; ++q) r[q] = v[q];
     }
     __syncthreads();
     /* wave 0 closes the stage alone */
@@ -1016,11 +1134,11 @@ __global__ __launch_bounds__(64 * NW) void k_stage_fused(Dev d, Epi e) {
 #pragma unroll
         for (int sp = 1; sp < NW; sp *= 2)
 #pragma unroll
-            for (int ww = 0; ww < NW; ww += 2 * sp) combine(hs[ww], ls[ww], hs[ww + sp], ls[ww + sp]);
+            for (int ww = 0; ww < NW; ww += 2 * sp) add_hilo(hs[ww], ls[ww], hs[ww + sp], ls[ww + sp]);
         const int ii = i0 + tt;
         const double k = u0 + e.c.co * ((double)hs[0] + (double)ls[0]);
         bad = !isfinite(k);
-        ys[tt * 3 + a] = stage_update(d, e, a * N + ii, ii, a, k, xv, rv, step);
+        ys[tt * 3 + a] = stage_update(d, e, a * N + ii, k, xv, rv, nz);
     }
     /* LDS operations of one wave complete in order: the fences only keep
      * the compiler from moving the reads of ys above its writes */
@@ -1034,8 +1152,9 @@ __global__ __launch_bounds__(64 * NW) void k_stage_fused(Dev d, Epi e) {
          * bit), then its partner term and its part of the next pack */
         const int q = tid >> 1, h = tid & 1;
         double f[2][3];
-        spring_forces_rs(e.c, ys + (2 * q) * 3, ys + (2 * q + 1) * 3, tp.x, tp.y, st, ct, f[0], f[1]);
-        store_pack_sphere_rs<SPLIT>(d, e.c, i0 + tid, ys + tid * 3, ys + (tid ^ 1) * 3, f[h], f[h ^ 1]);
+        const double id =
+            spring_forces_rs(e.c, ys + (2 * q) * 3, ys + (2 * q + 1) * 3, tp.x, tp.y, st, ct, f[0], f[1]);
+        store_pack_sphere_rs<SPLIT>(d, e.c, i0 + tid, ys + tid * 3, ys + (tid ^ 1) * 3, f[h], f[h ^ 1], id);
     }
 }
 
@@ -1104,15 +1223,19 @@ __global__ __launch_bounds__(256) void k_stage_wide(Dev d, Epi e) {
     }
     const int di = (i - off) >> 1; /* local dumbbell (off is even) */
     __syncthreads();
-    /* as in k_stage_fused: after the staging barrier, for wave 0 only */
-    advance_slots(d, e);
-    double st = 0.0, ct = 0.0;
+    /* as in k_stage_fused: after the staging barrier */
+    advance_step(d, e, step);
+    double st = 0.0, ct = 0.0, nz = 0.0;
     double2 tp = make_double2(0.0, 0.0);
     if (tid < ni) {
         const long long row = step & (d.ring - 1);
         st = d.tab[row * 8 + 2 * e.stage];
         ct = d.tab[row * 8 + 2 * e.stage + 1];
         tp = d.phitrig[(i0 >> 1) + (tid >> 1)];
+    }
+    if (e.c.noise && tid < 3 * ni) {
+        nz = stage_noise(e.c, i0 + tid / 3, step, tid % 3);
+        asm volatile("" : "+v"(nz)); /* formed here, not where the update needs it */
     }
 
     const float crr = e.c.crr;
@@ -1165,13 +1288,6 @@ __global__ __launch_bounds__(256) void k_stage_wide(Dev d, Epi e) {
         two_sum_acc(az, bz, pz);
     }
 
-    auto combine = [](float& hi, float& lo, float oh, float ol) {
-        const float s = hi + oh;
-        const float bb = s - hi;
-        const float err = (hi - (s - bb)) + (oh - bb);
-        hi = s;
-        lo = (lo + ol) + err;
-    };
     __syncthreads(); /* the sources are no longer read */
     float* red = reinterpret_cast<float*>(fs_lds);                   /* [4 waves][FW_I][6] */
     double* ys = reinterpret_cast<double*>(fs_lds) + 4 * FW_I * 3;   /* [FW_I][3] stage positions */
@@ -1191,13 +1307,13 @@ __global__ __launch_bounds__(256) void k_stage_wide(Dev d, Epi e) {
             hs[ww] = r[0];
             ls[ww] = r[1];
         }
-        combine(hs[0], ls[0], hs[1], ls[1]);
-        combine(hs[2], ls[2], hs[3], ls[3]);
-        combine(hs[0], ls[0], hs[2], ls[2]);
+        add_hilo(hs[0], ls[0], hs[1], ls[1]);
+        add_hilo(hs[2], ls[2], hs[3], ls[3]);
+        add_hilo(hs[0], ls[0], hs[2], ls[2]);
         const int ii = i0 + tt;
         const double k = u0 + e.c.co * ((double)hs[0] + (double)ls[0]);
         if (!isfinite(k)) *badf = 1;
-        ys[tt * 3 + a] = stage_update(d, e, a * N + ii, ii, a, k, xv, rv, step);
+        ys[tt * 3 + a] = stage_update(d, e, a * N + ii, k, xv, rv, nz);
     }
     __syncthreads();
     if (tid == 0 && *badf) atomicOr(&d.ctl->flag, FLAG_NONFINITE);
@@ -1205,8 +1321,9 @@ __global__ __launch_bounds__(256) void k_stage_wide(Dev d, Epi e) {
         /* one lane per sphere, as in k_stage_fused */
         const int q = tid >> 1, h = tid & 1;
         double f[2][3];
-        spring_forces_rs(e.c, ys + (2 * q) * 3, ys + (2 * q + 1) * 3, tp.x, tp.y, st, ct, f[0], f[1]);
-        store_pack_sphere_rs<SPLIT>(d, e.c, i0 + tid, ys + tid * 3, ys + (tid ^ 1) * 3, f[h], f[h ^ 1]);
+        const double id =
+            spring_forces_rs(e.c, ys + (2 * q) * 3, ys + (2 * q + 1) * 3, tp.x, tp.y, st, ct, f[0], f[1]);
+        store_pack_sphere_rs<SPLIT>(d, e.c, i0 + tid, ys + tid * 3, ys + (tid ^ 1) * 3, f[h], f[h ^ 1], id);
     }
 }
 
@@ -1242,7 +1359,7 @@ __global__ __launch_bounds__(256) void k_stage_wide(Dev d, Epi e) {
  * unit the early finishers' closing update overlaps the other work-group's
  * sums instead, and keeping pace was 6 % slower (N = 8192), as it was with
  * fewer chunks per lane (1-3 % at N = 512 and 2048). */
-template <int SPLIT, int RPY, int TI, int NW, int BAL>
+template <int SPLIT, int RPY, int TI, int NW, int BAL, int NOISE>
 __device__ __forceinline__ void stage_stream(const Dev& d, const Epi& e) {
     constexpr int G = 64 / TI;    /* lane groups (splits) per wave */
     constexpr int JS = NW * G;    /* source splits */
@@ -1318,13 +1435,16 @@ __device__ __forceinline__ void stage_stream(const Dev& d, const Epi& e) {
         }
     };
     fetch(0, std::integral_constant<int, 0>{});
-    put(0, std::integral_constant<int, 0>{});
+    /* With few sources per lane (4 or 8 targets) wave 0, which closes the
+     * stage, is what the work-group waits for: it reads the step index, issues
+     * the loads that depend on it and forms the noise while its first sources
+     * arrive. With 16 targets its sums are not the last to finish: sources go
+     * first, and the noise, whose code in front of the sums cost 1 to 2 % at
+     * N = 6000 and 8192 even unused, is formed at the update. */
+    if (TI == 16) put(0, std::integral_constant<int, 0>{});
     if (K > 1) fetch(1, std::integral_constant<int, 1>{});
-    /* wave 0 only: the step slots and this stage's (sin, cos)(omega t) and
-     * phases, whose dependent loads then stall a wave that is not the last
-     * to finish its sums */
-    advance_slots(d, e);
-    double st = 0.0, ct = 0.0;
+    advance_step(d, e, step);
+    double st = 0.0, ct = 0.0, nz = 0.0;
     double2 tp = make_double2(0.0, 0.0);
     if (tid < ni) {
         const long long row = step & (d.ring - 1);
@@ -1332,6 +1452,11 @@ __device__ __forceinline__ void stage_stream(const Dev& d, const Epi& e) {
         ct = d.tab[row * 8 + 2 * e.stage + 1];
         tp = d.phitrig[(i0 >> 1) + (tid >> 1)];
     }
+    if (NOISE && TI < 16 && tid < 3 * ni) {
+        nz = stage_noise(e.c, i0 + tid / 3, step, tid % 3);
+        asm volatile("" : "+v"(nz)); /* formed here, not where the update needs it */
+    }
+    if (TI < 16) put(0, std::integral_constant<int, 0>{});
 
     const float crr = e.c.crr;
     float ax = 0.f, ay = 0.f, az = 0.f, bx = 0.f, by = 0.f, bz = 0.f;
@@ -1397,21 +1522,21 @@ __device__ __forceinline__ void stage_stream(const Dev& d, const Epi& e) {
 
     /* combine the partial sums of each target as k_stage_fused does: the G
      * groups of a wave by shuffles, then the waves through LDS in a tree */
-    auto combine = [](float& hi, float& lo, float oh, float ol) {
-        const float s = hi + oh;
-        const float bb = s - hi;
-        const float err = (hi - (s - bb)) + (oh - bb);
-        hi = s;
-        lo = (lo + ol) + err;
-    };
+    float v[6] = {ax, bx, ay, by, az, bz};
+    if (TI == 16) {
+        /* sixteen waves keep the VALU busy: the exchanges go through the LDS
+         * crossbar instead (VALU swaps 1 % slower at N = 4096 and 8192; with 4
+         * or 8 targets the round trips' latency counts, 3 % at N = 512) */
 #pragma unroll
-    for (int sh = TI; sh < 64; sh *= 2) {
-        const float oax = __shfl_xor(ax, sh), obx = __shfl_xor(bx, sh);
-        const float oay = __shfl_xor(ay, sh), oby = __shfl_xor(by, sh);
-        const float oaz = __shfl_xor(az, sh), obz = __shfl_xor(bz, sh);
-        combine(ax, bx, oax, obx);
-        combine(ay, by, oay, oby);
-        combine(az, bz, oaz, obz);
+        for (int sh = 16; sh < 64; sh *= 2) {
+            float o[6];
+#pragma unroll
+            for (int q = 0; q < 6; ++q) o[q] = __shfl_xor(v[q], sh);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) add_hilo(v[2 * a], v[2 * a + 1], o[2 * a], o[2 * a + 1]);
+        }
+    } else {
+        wave_add_hilo<TI>(v);
     }
     /* the combination area lies beside the source slots, so no barrier
      * waits for the slowest wave's last reads before it is written */
@@ -1419,7 +1544,7 @@ __device__ __forceinline__ void stage_stream(const Dev& d, const Epi& e) {
     double* ys = reinterpret_cast<double*>(red + NW * TI * 6); /* [TI][3] stage positions */
     if (g == 0) {
         float* r = red + (w * TI + t) * 6;
-        r[0] = ax; r[1] = bx; r[2] = ay; r[3] = by; r[4] = az; r[5] = bz;
+        for (int q = 0; q < 6; ++q) r[q] = v[q];
     }
     __syncthreads();
     /* wave 0 closes the stage alone */
@@ -1438,11 +1563,12 @@ __device__ __forceinline__ void stage_stream(const Dev& d, const Epi& e) {
 #pragma unroll
         for (int st2 = 1; st2 < NW; st2 *= 2)
 #pragma unroll
-            for (int ww = 0; ww < NW; ww += 2 * st2) combine(hs[ww], ls[ww], hs[ww + st2], ls[ww + st2]);
+            for (int ww = 0; ww < NW; ww += 2 * st2) add_hilo(hs[ww], ls[ww], hs[ww + st2], ls[ww + st2]);
         const int ii = i0 + tt;
         const double k = u0 + e.c.co * ((double)hs[0] + (double)ls[0]);
         bad = !isfinite(k);
-        ys[tt * 3 + a] = stage_update(d, e, a * N + ii, ii, a, k, xv, rv, step);
+        if (NOISE && TI == 16) nz = stage_noise(e.c, ii, step, a);
+        ys[tt * 3 + a] = stage_update(d, e, a * N + ii, k, xv, rv, nz);
     }
     /* LDS operations of one wave complete in order: the fences only keep
      * the compiler from moving the reads of ys above its writes */
@@ -1453,23 +1579,26 @@ __device__ __forceinline__ void stage_stream(const Dev& d, const Epi& e) {
     if (tid < ni) {
         const int q = tid >> 1, h = tid & 1;
         double f[2][3];
-        spring_forces_rs(e.c, ys + (2 * q) * 3, ys + (2 * q + 1) * 3, tp.x, tp.y, st, ct, f[0], f[1]);
-        store_pack_sphere_rs<SPLIT>(d, e.c, i0 + tid, ys + tid * 3, ys + (tid ^ 1) * 3, f[h], f[h ^ 1]);
+        const double id =
+            spring_forces_rs(e.c, ys + (2 * q) * 3, ys + (2 * q + 1) * 3, tp.x, tp.y, st, ct, f[0], f[1]);
+        store_pack_sphere_rs<SPLIT>(d, e.c, i0 + tid, ys + tid * 3, ys + (tid ^ 1) * 3, f[h], f[h ^ 1], id);
     }
 }
 
-template <int SPLIT, int RPY, int TI, int NW>
+/* NOISE apart: its registers would not fit beside the others' in the capped
+ * instance below (11 spilled, 4 % at N = 8192 without noise) */
+template <int SPLIT, int RPY, int TI, int NW, int NOISE>
 __global__ __launch_bounds__(64 * NW) void k_stage_stream(Dev d, Epi e) {
-    stage_stream<SPLIT, RPY, TI, NW, TI == 16 && NW == 16>(d, e);
+    stage_stream<SPLIT, RPY, TI, NW, TI == 16 && NW == 16, NOISE>(d, e);
 }
 
 /* The same with registers capped for 8 waves per SIMD (63 VGPRs), so that two
  * 16-wave work-groups share a compute unit: for launches of more than 256
  * work-groups (N = 8192: 4 % faster per step; with one work-group per compute
  * unit, N = 4096, the cap cost 5 %). */
-template <int SPLIT, int RPY, int TI, int NW>
+template <int SPLIT, int RPY, int TI, int NW, int NOISE>
 __global__ __launch_bounds__(64 * NW, 8) void k_stage_stream_x2(Dev d, Epi e) {
-    stage_stream<SPLIT, RPY, TI, NW, 0>(d, e);
+    stage_stream<SPLIT, RPY, TI, NW, 0, NOISE>(d, e);
 }
 
 /* FP64 streamed form of the fused stage (AD_FP64_TILED with
@@ -1498,17 +1627,6 @@ __device__ __forceinline__ void pair_term64(double ir, double rx, double ry, dou
         py = __builtin_fma(ir, __builtin_fma(tt, ry, Fy), py);
         pz = __builtin_fma(ir, __builtin_fma(tt, rz, Fz), pz);
     }
-}
-
-/* 1/sqrt(r2) from v_rsq_f64 (about 2^-24) and one third-order step
- * y (1 + e/2 + 3 e^2/8), e = 1 - r2 y^2: within an ulp. (One Newton step, two
- * instructions fewer, leaves 4e-15.) */
-__device__ __forceinline__ double rsqrt64(double r2) {
-    const double y = __builtin_amdgcn_rsq(r2);
-    const double g = r2 * y;
-    const double e = __builtin_fma(-g, y, 1.0);
-    const double p = __builtin_fma(e, 0.375, 0.5);
-    return __builtin_fma(y * e, p, y);
 }
 
 template <int RPY, int TI>
@@ -1575,9 +1693,8 @@ __global__ __launch_bounds__(1024) void k_stage_stream64(Dev d, Epi e) {
         sF[x] = eF;
     };
     fetch(0);
-    put(0);
-    advance_slots(d, e);
-    double st = 0.0, ct = 0.0;
+    advance_step(d, e, step);
+    double st = 0.0, ct = 0.0, nz = 0.0;
     double2 tp = make_double2(0.0, 0.0);
     if (tid < ni) {
         const long long row = step & (d.ring - 1);
@@ -1585,6 +1702,11 @@ __global__ __launch_bounds__(1024) void k_stage_stream64(Dev d, Epi e) {
         ct = d.tab[row * 8 + 2 * e.stage + 1];
         tp = d.phitrig[(i0 >> 1) + (tid >> 1)];
     }
+    if (e.c.noise && tid < 3 * ni) {
+        nz = stage_noise(e.c, i0 + tid / 3, step, tid % 3);
+        asm volatile("" : "+v"(nz)); /* formed here, not where the update needs it */
+    }
+    put(0);
 
     const double crr = e.c.crr64;
     double px = 0.0, py = 0.0, pz = 0.0;
@@ -1650,7 +1772,7 @@ __global__ __launch_bounds__(1024) void k_stage_stream64(Dev d, Epi e) {
         const int ii = i0 + tt;
         const double k = u0 + e.c.co * hs[0];
         bad = !isfinite(k);
-        ys[tt * 3 + a] = stage_update(d, e, a * N + ii, ii, a, k, xv, rv, step);
+        ys[tt * 3 + a] = stage_update(d, e, a * N + ii, k, xv, rv, nz);
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -2056,7 +2178,7 @@ __global__ __launch_bounds__(64 * (NP + 1)) void k_pairs_f64w(Dev d, Epi e, int 
     constexpr int BUF = ROWS * RS; /* doubles per chunk buffer */
     extern __shared__ __align__(16) double w_lds[]; /* [2 sets][NP chunks][ROWS][RS] */
     const Item it = d.fitems[blockIdx.x];
-    if (mode) advance_slots(d, e);
+    if (mode && !e.pack_next) advance_slots(d, e);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l = threadIdx.x & 63;
     const int Nb = it.Nb, off = it.ioff;
@@ -2073,7 +2195,7 @@ __global__ __launch_bounds__(64 * (NP + 1)) void k_pairs_f64w(Dev d, Epi e, int 
         const bool cl = l < 3 * TW && l - ca * TW < it.ni;
         double u0 = 0.0, xv = 0.0, rv = 0.0, st = 0.0, ct = 0.0;
         double2 tp = make_double2(0.0, 0.0);
-        long long step = 0;
+        double nz = 0.0;
         if (close) {
             if (cl) {
                 const int o = ca * d.Ntot + ci;
@@ -2084,7 +2206,9 @@ __global__ __launch_bounds__(64 * (NP + 1)) void k_pairs_f64w(Dev d, Epi e, int 
                 }
             }
             if (!e.u_aos) {
-                step = d.ctl->slot[e.stage > 0];
+                const long long step = d.ctl->slot[e.stage > 0];
+                advance_step(d, e, step);
+                if (cl) nz = stage_noise(e.c, ci, step, ca);
                 const long long row = step & (d.ring - 1);
                 if (l < it.ni) {
                     st = d.tab[row * 8 + 2 * e.stage];
@@ -2141,7 +2265,7 @@ __global__ __launch_bounds__(64 * (NP + 1)) void k_pairs_f64w(Dev d, Epi e, int 
             if (e.u_aos)
                 e.u_aos[3 * ci + ca] = k;
             else
-                y = stage_update(d, e, ca * d.Ntot + ci, ci, ca, k, xv, rv, step);
+                y = stage_update(d, e, ca * d.Ntot + ci, k, xv, rv, nz);
         }
         if (__any(nf) && l == 0) atomicOr(&d.ctl->flag, FLAG_NONFINITE);
         if (e.u_aos) return;
@@ -2517,16 +2641,7 @@ __device__ __forceinline__ double res_update(const Coef& c, int integ, int stage
  * the sums of lane (itself xor distance) and adds them in with TwoSum. */
 __device__ __forceinline__ void combine_hilo(float v[6], const float o[6]) {
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        float& hi = v[2 * a];
-        float& lo = v[2 * a + 1];
-        const float oh = o[2 * a], ol = o[2 * a + 1];
-        const float s = hi + oh;
-        const float bb = s - hi;
-        const float err = (hi - (s - bb)) + (oh - bb);
-        hi = s;
-        lo = (lo + ol) + err;
-    }
+    for (int a = 0; a < 3; ++a) add_hilo(v[2 * a], v[2 * a + 1], o[2 * a], o[2 * a + 1]);
 }
 /* distances 1 and 2 through DPP quad permutations (CTRL 0xB1 swaps the lanes
  * of each pair, 0x4E the pairs of each quad): a VALU operation, no LDS round
@@ -3067,13 +3182,31 @@ static hipError_t go_wide(const Dev& d, const Epi& e, int maxNb, hipStream_t s, 
     return hipGetLastError();
 }
 
-template <int SPLIT, int RPY>
-static hipError_t go_stream(const Dev& d, const Epi& e, hipStream_t s, const Timing& tm) {
+typedef void (*StageKernel)(Dev, Epi);
+
+template <int SPLIT, int RPY, int NOISE>
+static StageKernel stream_kernel(int ti, int x2) {
+    if (ti == 16) return x2 ? k_stage_stream_x2<SPLIT, RPY, 16, 16, NOISE> : k_stage_stream<SPLIT, RPY, 16, 16, NOISE>;
+    return ti == 8 ? k_stage_stream<SPLIT, RPY, 8, 8, NOISE> : k_stage_stream<SPLIT, RPY, 4, 8, NOISE>;
+}
+static StageKernel stream_kernel(int split, int rpy, int noise, int ti, int x2) {
+    switch (split * 4 + rpy * 2 + noise) {
+        case 0: return stream_kernel<0, 0, 0>(ti, x2);
+        case 1: return stream_kernel<0, 0, 1>(ti, x2);
+        case 2: return stream_kernel<0, 1, 0>(ti, x2);
+        case 3: return stream_kernel<0, 1, 1>(ti, x2);
+        case 4: return stream_kernel<1, 0, 0>(ti, x2);
+        case 5: return stream_kernel<1, 0, 1>(ti, x2);
+        case 6: return stream_kernel<1, 1, 0>(ti, x2);
+        default: return stream_kernel<1, 1, 1>(ti, x2);
+    }
+}
+
+static hipError_t go_stream(const Dev& d, const Epi& e, const Shape& sh, hipStream_t s, const Timing& tm) {
     const int ti = stream_targets(d.Ntot), nw = stream_waves(ti);
-    const int lds = fused_stream_lds_bytes(SPLIT, nw, ti);
+    const int lds = fused_stream_lds_bytes(sh.split, nw, ti);
     const dim3 grid(d.nfitems ? d.nfitems : (d.Ntot + ti - 1) / ti);
-    auto kern = ti == 16 ? (grid.x > 256 ? k_stage_stream_x2<SPLIT, RPY, 16, 16> : k_stage_stream<SPLIT, RPY, 16, 16>)
-                : ti == 8 ? k_stage_stream<SPLIT, RPY, 8, 8> : k_stage_stream<SPLIT, RPY, 4, 8>;
+    auto kern = stream_kernel(sh.split ? 1 : 0, sh.rpy ? 1 : 0, e.c.noise ? 1 : 0, ti, grid.x > 256);
     if (tm.start)
         hipExtLaunchKernelGGL(kern, grid, dim3(64 * nw), lds, s, tm.start, tm.stop, 0, d, e);
     else
@@ -3122,22 +3255,7 @@ static ResidentKernel resident_c_kernel(int hilo, int rpy, int T, int integ) {
 }
 
 hipError_t prepare_fused() {
-    const void* kernels[] = {reinterpret_cast<const void*>(&k_stage_stream<0, 0, 16, 16>),
-                             reinterpret_cast<const void*>(&k_stage_stream<0, 1, 16, 16>),
-                             reinterpret_cast<const void*>(&k_stage_stream<1, 0, 16, 16>),
-                             reinterpret_cast<const void*>(&k_stage_stream<1, 1, 16, 16>),
-                             reinterpret_cast<const void*>(&k_stage_stream_x2<0, 0, 16, 16>),
-                             reinterpret_cast<const void*>(&k_stage_stream_x2<0, 1, 16, 16>),
-                             reinterpret_cast<const void*>(&k_stage_stream_x2<1, 0, 16, 16>),
-                             reinterpret_cast<const void*>(&k_stage_stream_x2<1, 1, 16, 16>),
-                             reinterpret_cast<const void*>(&k_stage_stream<0, 0, 8, 8>),
-                             reinterpret_cast<const void*>(&k_stage_stream<0, 1, 8, 8>),
-                             reinterpret_cast<const void*>(&k_stage_stream<1, 0, 8, 8>),
-                             reinterpret_cast<const void*>(&k_stage_stream<1, 1, 8, 8>),
-                             reinterpret_cast<const void*>(&k_stage_stream<0, 0, 4, 8>),
-                             reinterpret_cast<const void*>(&k_stage_stream<0, 1, 4, 8>),
-                             reinterpret_cast<const void*>(&k_stage_stream<1, 0, 4, 8>),
-                             reinterpret_cast<const void*>(&k_stage_stream<1, 1, 4, 8>),
+    const void* kernels[] = {
                              reinterpret_cast<const void*>(&k_stage_stream64<0, 16>),
                              reinterpret_cast<const void*>(&k_stage_stream64<1, 16>),
                              reinterpret_cast<const void*>(&k_stage_stream64<0, 8>),
@@ -3156,6 +3274,17 @@ hipError_t prepare_fused() {
                              reinterpret_cast<const void*>(&k_stage_fused<0, 1, 4>),
                              reinterpret_cast<const void*>(&k_stage_fused<1, 0, 4>),
                              reinterpret_cast<const void*>(&k_stage_fused<1, 1, 4>)};
+    const void* stream[32];
+    for (int q = 0; q < 32; ++q) /* hi/lo, RPY, noise; 16 targets with and without the cap, 8, 4 */
+        stream[q] = reinterpret_cast<const void*>(
+            stream_kernel(q & 1, (q >> 1) & 1, (q >> 2) & 1, q < 16 ? 16 : q < 24 ? 8 : 4, q < 8));
+    for (const void* k : stream) {
+        hipError_t err = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, FUSED_LDS_MAX);
+        if (err != hipSuccess) {
+            (void)hipGetLastError();
+            return err;
+        }
+    }
     for (const void* k : kernels) {
         hipError_t err = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, FUSED_LDS_MAX);
         if (err != hipSuccess) {
@@ -3220,10 +3349,7 @@ hipError_t launch_fused(const Dev& d, const Epi& e, const Shape& sh, int maxNb, 
         return sh.rpy ? go_wide<0, 1>(d, e, maxNb, s, tm0) : go_wide<0, 0>(d, e, maxNb, s, tm0);
     }
     if ((d.nsys > 1) != (d.nfitems > 0)) return hipErrorInvalidValue;
-    if (sh.fused == 3) {
-        if (sh.split) return sh.rpy ? go_stream<1, 1>(d, e, s, tm0) : go_stream<1, 0>(d, e, s, tm0);
-        return sh.rpy ? go_stream<0, 1>(d, e, s, tm0) : go_stream<0, 0>(d, e, s, tm0);
-    }
+    if (sh.fused == 3) return go_stream(d, e, sh, s, tm0);
     if (sh.fused != 1) return hipErrorInvalidValue;
     const int nw = d.nsys > 1 ? 4 : 16;
     if (fused_lds_bytes(maxNb, sh.split, nw) > FUSED_LDS_MAX) return hipErrorInvalidValue;
