@@ -152,6 +152,33 @@ __device__ __forceinline__ void advance_step(const Dev& d, const Epi& e, long lo
     if (e.stage == e.nst - 1) d.ctl->slot[0] = step + 1;
 }
 
+/* x[q] = 1/sqrt(x[q]) (v_rsq_f32) for four terms together, set apart from the
+ * instructions around them by a scalar one on each side.
+ * A SIMD issues vector instructions of two waves at once (measured: 1.7 to 1.9
+ * wave instructions per compute unit and clock for streams of multiplies or
+ * FMAs), but after a v_rsq_f32 it stays at one (0.93 for 17 such instructions
+ * and one v_rsq_f32, 79 cycles) until something else than a vector instruction
+ * comes between. With a scalar instruction before and after it is 48 cycles
+ * per 18 instructions, 45 with four v_rsq_f32 together (with the loads of a
+ * source per 18 instructions 50 to 56, from 58 to 61). The scalar instruction
+ * is a priority change (PRIO: raised over the group, a little faster still) or
+ * s_nop where a kernel sets priorities itself. */
+template <int PRIO>
+__device__ __forceinline__ void rsq4(float x[4]) {
+    if (PRIO)
+        asm("s_setprio 3\n\tv_rsq_f32 %0, %0\n\tv_rsq_f32 %1, %1\n\tv_rsq_f32 %2, %2\n\tv_rsq_f32 %3, %3\n\t"
+            "s_setprio 0"
+            : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
+    else
+        asm("s_nop 0\n\tv_rsq_f32 %0, %0\n\tv_rsq_f32 %1, %1\n\tv_rsq_f32 %2, %2\n\tv_rsq_f32 %3, %3\n\ts_nop 0"
+            : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
+}
+/* and for one */
+__device__ __forceinline__ float rsq1(float x) {
+    asm("s_setprio 3\n\tv_rsq_f32 %0, %0\n\ts_setprio 0" : "+v"(x));
+    return x;
+}
+
 /* Launch shape of the pair kernel: WG threads = (WG/64/wj) waves on distinct
  * targets x wj waves splitting each j-tile; ipl targets per lane; split = 1
  * for hi/lo positions (FP32C only). One work item covers 64*ipl*WG/64/wj
@@ -224,12 +251,12 @@ hipError_t launch_pairs_sym(const Dev& d, const Epi& e, const Shape& sh, hipStre
 /* The systems it takes. It saves instructions, most with hi/lo positions and
  * with steric forces (whose other kernel tests every pair's distance), and
  * pays for partial sums at both ends of a pair. us per RK4 step against the
- * ordered pair kernel: hi/lo 9000 spheres 245 (237), 10000 290 (297), 12000
- * 362 (377), 20000 844 (965), 65536 6.9 ms (9.15); single-float 15002 407
- * (408), 17000 537 (571), 32768 1710 (1967); steric 8300 225 (277), 15002 460
- * (586), 65536 7.1 ms (9.0). */
+ * ordered pair kernel: hi/lo 8192 spheres 195 (190), 9000 226 (242), 12000 325
+ * (335); single-float 12000 295 (301), 13000 335 (334), 14000 353 (381), 15002
+ * 389 (426); steric, hi/lo 3000 128 (128), 4096 135 (153), 6000 171 (206);
+ * steric, single-float 3000 118 (171), 5000 136 (192). */
 inline bool sym_takes(int N, int hilo, int steric) {
-    return N >= (steric ? 8192 : hilo ? 9728 : 16384);
+    return N >= (steric ? 4096 : hilo ? 8704 : 13312);
 }
 /* spheres per block: work-groups of 4 or 8 waves, 128 spheres per wave (the
  * larger block halves the partial sums of the largest systems) */

@@ -654,6 +654,45 @@ __device__ __forceinline__ void pair_term(float ir, float rx, float ry, float rz
     }
 }
 
+/* A lane's target position in the fused stage kernels (lo: hi/lo positions only) */
+struct Target {
+    float hx, hy, hz, lx, ly, lz;
+};
+
+/* Four terms of a fused stage, from the LDS entries x0, x0 + dx, x0 + 2 dx and
+ * x0 + 3 dx: none masked. Their v_rsq_f32 together, see rsq4. */
+template <int SPLIT, int RPY, int PRIO>
+__device__ __forceinline__ void four_terms(const Target& t, const float4* sA, const float4* sB, const float* sC,
+                                           const float2* sF, int x0, int dx, float crr, float& px, float& py,
+                                           float& pz) {
+    float rx[4], ry[4], rz[4], fx[4], fy[4], fz[4], ir[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int x = x0 + u * dx;
+        const float4 A = sA[x];
+        fx[u] = A.w;
+        if (SPLIT) {
+            const float4 B = sB[x];
+            fy[u] = B.w;
+            fz[u] = sC[x];
+            rx[u] = (t.hx - A.x) + (t.lx - B.x);
+            ry[u] = (t.hy - A.y) + (t.ly - B.y);
+            rz[u] = (t.hz - A.z) + (t.lz - B.z);
+        } else {
+            const float2 f = sF[x];
+            fy[u] = f.x;
+            fz[u] = f.y;
+            rx[u] = t.hx - A.x;
+            ry[u] = t.hy - A.y;
+            rz[u] = t.hz - A.z;
+        }
+        ir[u] = __builtin_fmaf(rz[u], rz[u], __builtin_fmaf(ry[u], ry[u], rx[u] * rx[u]));
+    }
+    rsq4<PRIO>(ir);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) pair_term<RPY>(ir[u], rx[u], ry[u], rz[u], fx[u], fy[u], fz[u], crr, px, py, pz);
+}
+
 /* One thread's entry of a source tile: sphere t0 + t of the pack, or
  * padding (far away and force-free, so it contributes exactly zero). */
 __device__ __forceinline__ void load_tile_entry(const Dev& d, int t0, int jend, int t, float4& A, float4& B,
@@ -724,7 +763,7 @@ __global__ __launch_bounds__(WG) void k_pairs_f32c(Dev d, Epi e, int mode) {
     if (mode) advance_slots(d, e);
     const int t = threadIdx.x;
     const int lane = t & 63;
-    const int wave = t >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wi = wave % WI;
     const int wj = wave / WI;
     const int slot = wi * 64 + lane;          /* target slot inside the block */
@@ -775,29 +814,37 @@ __global__ __launch_bounds__(WG) void k_pairs_f32c(Dev d, Epi e, int mode) {
         if (!diag) {
             const int n4 = (nw + 3) & ~3;
             for (int jj = jb; jj < jb + n4; jj += 4) {
+                float4 Aj[4], Bj[4];
+                float Fz[4], rx[IPL][4], ry[IPL][4], rz[IPL][4], ir[IPL][4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const float4 Aj = sA[jj + u];
-                    const float4 Bj = sB[jj + u];
-                    const float Fz = sC[jj + u];
+                    Aj[u] = sA[jj + u];
+                    Bj[u] = sB[jj + u];
+                    Fz[u] = sC[jj + u];
 #pragma unroll
                     for (int q = 0; q < IPL; ++q) {
-                        float rx, ry, rz;
                         if (SPLIT) {
-                            rx = (hx[q] - Aj.x) + (lx[q] - Bj.x);
-                            ry = (hy[q] - Aj.y) + (ly[q] - Bj.y);
-                            rz = (hz[q] - Aj.z) + (lz[q] - Bj.z);
+                            rx[q][u] = (hx[q] - Aj[u].x) + (lx[q] - Bj[u].x);
+                            ry[q][u] = (hy[q] - Aj[u].y) + (ly[q] - Bj[u].y);
+                            rz[q][u] = (hz[q] - Aj[u].z) + (lz[q] - Bj[u].z);
                         } else {
-                            rx = hx[q] - Aj.x;
-                            ry = hy[q] - Aj.y;
-                            rz = hz[q] - Aj.z;
+                            rx[q][u] = hx[q] - Aj[u].x;
+                            ry[q][u] = hy[q] - Aj[u].y;
+                            rz[q][u] = hz[q] - Aj[u].z;
                         }
-                        float r2 = __builtin_fmaf(rz, rz, __builtin_fmaf(ry, ry, rx * rx));
-                        if (STERIC && r2 < d.list_r2) add_candidate(d, ib + q, iend, t0 + jj + u);
-                        float ir = __builtin_amdgcn_rsqf(r2);
-                        pair_term<RPY>(ir, rx, ry, rz, Aj.w, Bj.w, Fz, crr, px[q], py[q], pz[q]);
+                        ir[q][u] = __builtin_fmaf(rz[q][u], rz[q][u],
+                                                  __builtin_fmaf(ry[q][u], ry[q][u], rx[q][u] * rx[q][u]));
+                        if (STERIC && ir[q][u] < d.list_r2) add_candidate(d, ib + q, iend, t0 + jj + u);
                     }
                 }
+#pragma unroll
+                for (int q = 0; q < IPL; ++q) rsq4<1>(ir[q]);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int q = 0; q < IPL; ++q)
+                        pair_term<RPY>(ir[q][u], rx[q][u], ry[q][u], rz[q][u], Aj[u].w, Bj[u].w, Fz[u], crr, px[q],
+                                       py[q], pz[q]);
             }
         } else {
             for (int jj = jb; jj < jb + nw; ++jj) {
@@ -1081,22 +1128,29 @@ __global__ __launch_bounds__(64 * NW) void k_stage_fused(Dev d, Epi e) {
         if (masked && (j >> 1) == di) ir = 0.f;
         pair_term<RPY>(ir, rx, ry, rz, Aj.w, Fy, Fz, crr, px, py, pz);
     };
+    const Target me{hx, hy, hz, lx, ly, lz};
+    auto quad = [&](int x0, int dx, float& px, float& py, float& pz) {
+        four_terms<SPLIT, RPY, 1>(me, sA, sB, sC, sF, x0, dx, crr, px, py, pz);
+    };
     const int M = np / JS;
     const int ms = (i0 - off) / JS; /* the source block holding this group's dumbbells */
     for (int m0 = 0; m0 < M; m0 += FS_M) {
         const int m1 = min(M, m0 + FS_M);
         float px = 0.f, py = 0.f, pz = 0.f;
         if (ms >= m0 && ms < m1) {
-#pragma unroll 4
-            for (int m = m0; m < ms; ++m) term(js + JS * m, false, px, py, pz);
+            int m = m0;
+            for (; m + 4 <= ms; m += 4) quad(js + JS * m, JS, px, py, pz);
+            for (; m < ms; ++m) term(js + JS * m, false, px, py, pz);
             term(js + JS * ms, true, px, py, pz);
-#pragma unroll 4
-            for (int m = ms + 1; m < m1; ++m) term(js + JS * m, false, px, py, pz);
+            for (m = ms + 1; m + 4 <= m1; m += 4) quad(js + JS * m, JS, px, py, pz);
+            for (; m < m1; ++m) term(js + JS * m, false, px, py, pz);
         } else if (m1 - m0 == FS_M) {
-#pragma unroll 4
-            for (int m = m0; m < m0 + FS_M; ++m) term(js + JS * m, false, px, py, pz);
+#pragma unroll 2
+            for (int m = m0; m < m0 + FS_M; m += 4) quad(js + JS * m, JS, px, py, pz);
         } else {
-            for (int m = m0; m < m1; ++m) term(js + JS * m, false, px, py, pz);
+            int m = m0;
+            for (; m + 4 <= m1; m += 4) quad(js + JS * m, JS, px, py, pz);
+            for (; m < m1; ++m) term(js + JS * m, false, px, py, pz);
         }
         two_sum_acc(ax, bx, px);
         two_sum_acc(ay, by, py);
@@ -1195,7 +1249,7 @@ __global__ __launch_bounds__(256) void k_stage_wide(Dev d, Epi e) {
         xv = d.X[o];
         if (e.stage > 0) rv = d.R[o];
     }
-    const int w = tid >> 6, l = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
     const int i = i0 + l;
     /* this lane's target position (lanes past the block's end sum for
      * position zero and are not used) */
@@ -1268,6 +1322,10 @@ __global__ __launch_bounds__(256) void k_stage_wide(Dev d, Epi e) {
         if (masked && (j >> 1) == di) ir = 0.f;
         pair_term<RPY>(ir, rx, ry, rz, Aj.w, Fy, Fz, crr, px, py, pz);
     };
+    const Target me{hx, hy, hz, lx, ly, lz};
+    auto quad = [&](int x0, int dx, float& px, float& py, float& pz) {
+        four_terms<SPLIT, RPY, 1>(me, sA, sB, sC, sF, x0, dx, crr, px, py, pz);
+    };
     /* this wave's quarter of the sources, and the part of it that holds the
      * work-group's own spheres (local [i0 - off, i0 - off + ni)) */
     const int j0 = w * Q, j1 = j0 + Q;
@@ -1278,10 +1336,11 @@ __global__ __launch_bounds__(256) void k_stage_wide(Dev d, Epi e) {
         if (c0 < jm1 && c1 > jm0) {
             for (int j = c0; j < c1; ++j) term(j, true, px, py, pz);
         } else if (c1 - c0 == FW_M) {
-#pragma unroll 4
-            for (int j = c0; j < c0 + FW_M; ++j) term(j, false, px, py, pz);
+            for (int j = c0; j < c0 + FW_M; j += 4) quad(j, 1, px, py, pz);
         } else {
-            for (int j = c0; j < c1; ++j) term(j, false, px, py, pz);
+            int j = c0;
+            for (; j + 4 <= c1; j += 4) quad(j, 1, px, py, pz);
+            for (; j < c1; ++j) term(j, false, px, py, pz);
         }
         two_sum_acc(ax, bx, px);
         two_sum_acc(ay, by, py);
@@ -1484,9 +1543,13 @@ __device__ __forceinline__ void stage_stream(const Dev& d, const Epi& e) {
             rz = hz - Aj.z;
         }
         const float r2 = __builtin_fmaf(rz, rz, __builtin_fmaf(ry, ry, rx * rx));
-        float ir = __builtin_amdgcn_rsqf(r2);
+        float ir = BAL ? __builtin_amdgcn_rsqf(r2) : rsq1(r2);
         if (masked && (j >> 1) == di) ir = 0.f;
         pair_term<RPY>(ir, rx, ry, rz, Aj.w, Fy, Fz, crr, px, py, pz);
+    };
+    const Target me{hx, hy, hz, lx, ly, lz};
+    auto quad = [&](int x0, int dx, float& px, float& py, float& pz) {
+        four_terms<SPLIT, RPY, !BAL>(me, sA, sB, sC, sF, x0, dx, crr, px, py, pz);
     };
     float px = 0.f, py = 0.f, pz = 0.f;
     auto chunk = [&](int k, auto R) {
@@ -1504,8 +1567,13 @@ __device__ __forceinline__ void stage_stream(const Dev& d, const Epi& e) {
         if (own_wave && k == ko) {
             for (int v = 0; v < TI; ++v) term(x0 + v, j0 + v, true, px, py, pz);
         } else {
+            if (TI == 16 && !BAL) {
 #pragma unroll
-            for (int v = 0; v < TI; ++v) term(x0 + v, j0 + v, false, px, py, pz);
+                for (int v = 0; v < TI; ++v) term(x0 + v, j0 + v, false, px, py, pz);
+            } else {
+#pragma unroll
+                for (int v = 0; v < TI; v += 4) quad(x0 + v, 1, px, py, pz);
+            }
         }
         if ((k + 1) % FOLD == 0 || k + 1 == K) {
             two_sum_acc(ax, bx, px);

@@ -33,10 +33,8 @@
  * where some pair is closer.
  *
  * What bounds it is VALU issue: 15 instructions per ordered term (18.3 with
- * hi/lo positions) where the ordered sum takes 18.25 (24), at 1.17 wave
- * instructions per compute unit and clock (1.25 there: two in three are
- * three-operand FMAs, which issue in pairs less often). 65536 spheres with
- * hi/lo positions and steric forces: 1.75 ms per stage against 2.29.
+ * hi/lo positions) where the ordered sum takes 18.25 (24). 65536 spheres with
+ * hi/lo positions and steric forces: 1.6 ms per stage, the ordered sum 2.29.
  */
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
@@ -55,13 +53,27 @@ __device__ __forceinline__ void fold(float& hi, float& lo, float v) {
     lo = lo + e;
 }
 
-/* the value of the lane that DPP control CTRL names */
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+/* x[q] = 1/sqrt(x[q]) (v_rsq_f32), and (qx, qy, qz) from the neighbour in the
+ * pair of lanes (ROW = 0) or from two lanes on in the row of 16, the first two
+ * after its last (ROW = 1). Both kinds end the issue of two waves' vector
+ * instructions at once (see rsq4): together, between two scalar instructions,
+ * once per step (65536 spheres hi/lo 6.21 ms per RK4 step, 6.43 with the moves
+ * left to the compiler, 6.95 with neither set apart). Moves read registers
+ * written two instructions before at the latest, as DPP needs. */
+#define AD_MOVE3(CTRL)                                                              \
+    "v_mov_b32_dpp %0, %0 " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"     \
+    "v_mov_b32_dpp %1, %1 " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"     \
+    "v_mov_b32_dpp %2, %2 " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"
+template <int ROW>
+__device__ __forceinline__ void rsq_move(float x[2], float& qx, float& qy, float& qz) {
+    if (ROW)
+        asm("s_setprio 3\n\tv_rsq_f32 %3, %3\n\tv_rsq_f32 %4, %4\n\t" AD_MOVE3("row_ror:14") "s_setprio 0"
+            : "+v"(qx), "+v"(qy), "+v"(qz), "+v"(x[0]), "+v"(x[1]));
+    else
+        asm("s_setprio 3\n\tv_rsq_f32 %3, %3\n\tv_rsq_f32 %4, %4\n\t" AD_MOVE3("quad_perm:[1,0,3,2]") "s_setprio 0"
+            : "+v"(qx), "+v"(qy), "+v"(qz), "+v"(x[0]), "+v"(x[1]));
 }
-constexpr int PAIR_SWAP = 0xB1;  /* quad_perm [1,0,3,2] */
-constexpr int ROW_PLUS_2 = 0x12E; /* row_ror:14: lane c of a row of 16 takes lane c + 2 mod 16 */
+#undef AD_MOVE3
 
 /* append source j to the steric candidate list of target i */
 __device__ __forceinline__ void append(int* cnt, int* idx, int* flag, int i, int j) {
@@ -76,9 +88,9 @@ __device__ __forceinline__ void append(int* cnt, int* idx, int* flag, int i, int
 template <int RPY>
 struct Pair {
     float rx, ry, rz, ir, ir2, av, bw;
-    __device__ __forceinline__ void set(float x, float y, float z, float r2, bool skip, float crr) {
+    __device__ __forceinline__ void set(float x, float y, float z, float inv, float crr) {
         rx = x; ry = y; rz = z;
-        ir = skip ? 0.f : __builtin_amdgcn_rsqf(r2);
+        ir = inv;
         ir2 = ir * ir;
         if (RPY) {
             const float ir3 = ir * ir2;
@@ -191,7 +203,7 @@ __global__ __launch_bounds__(64 * NW) void k_pairs_sym(Dev d, Epi e) {
                     if (STERIC && r2 < d.list_r2 && j != ib + q && ib + q < N)
                         append(d.nbr_cnt, d.nbr_idx, &d.ctl->flag, ib + q, j);
                     Pair<RPY> pr;
-                    pr.set(rx, ry, rz, r2, (j >> 1) == (ib >> 1), crr);
+                    pr.set(rx, ry, rz, (j >> 1) == (ib >> 1) ? 0.f : rsq1(r2), crr);
                     pr.add(A.w, F.x, F.y, px[q], py[q], pz[q]);
                 }
             }
@@ -207,29 +219,27 @@ __global__ __launch_bounds__(64 * NW) void k_pairs_sym(Dev d, Epi e) {
                     const int at = x[(u ^ (u >> 1)) & 1] + (u & ~1);
                     const float4 A = sA[b][at], B = SPLIT ? sB[b][at] : A;
                     const float2 F = sF[b][at];
-                    unsigned r2min[IPL];
+                    float rx[IPL], ry[IPL], rz[IPL], ir[IPL];
+#pragma unroll
+                    for (int q = 0; q < IPL; ++q) ir[q] = separation(q, A, B, rx[q], ry[q], rz[q]);
+                    if (STERIC) {
+                        rmin = min(rmin, min(__builtin_bit_cast(unsigned, ir[0]), __builtin_bit_cast(unsigned, ir[1])));
+                        asm volatile("" : "+v"(rmin));
+                    }
                     if (u & 1) {
-                        qx = dpp<PAIR_SWAP>(qx);
-                        qy = dpp<PAIR_SWAP>(qy);
-                        qz = dpp<PAIR_SWAP>(qz);
+                        rsq_move<0>(ir, qx, qy, qz);
                     } else if (u > 0) {
-                        qx = dpp<ROW_PLUS_2>(qx);
-                        qy = dpp<ROW_PLUS_2>(qy);
-                        qz = dpp<ROW_PLUS_2>(qz);
+                        rsq_move<1>(ir, qx, qy, qz);
+                    } else {
+                        ir[0] = rsq1(ir[0]);
+                        ir[1] = rsq1(ir[1]);
                     }
 #pragma unroll
                     for (int q = 0; q < IPL; ++q) {
-                        float rx, ry, rz;
-                        const float r2 = separation(q, A, B, rx, ry, rz);
-                        r2min[q] = __builtin_bit_cast(unsigned, r2);
                         Pair<RPY> pr;
-                        pr.set(rx, ry, rz, r2, false, crr);
+                        pr.set(rx[q], ry[q], rz[q], ir[q], crr);
                         pr.add(A.w, F.x, F.y, px[q], py[q], pz[q]);
                         pr.add(fx[q], fy[q], fz[q], qx, qy, qz);
-                    }
-                    if (STERIC) {
-                        rmin = min(rmin, min(r2min[0], r2min[1]));
-                        asm volatile("" : "+v"(rmin));
                     }
                     /* each step's sums are formed in it: left alone, the
                      * compiler puts off one side of all 16 steps and

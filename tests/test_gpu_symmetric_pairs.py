@@ -25,8 +25,8 @@ def _displacements(params, X, phi, n, **kw):
 
 
 @pytest.mark.parametrize("tensor", ["oseen", "rpy"])
-@pytest.mark.parametrize("N,posmode", [(9728, 1), (9730, 1), (9792, 1), (10238, 1), (10242, 1), (32770, 1),
-                                       (16384, 2), (16898, 2), (33794, 2)])
+@pytest.mark.parametrize("N,posmode", [(8704, 1), (9728, 1), (9730, 1), (9792, 1), (10238, 1), (10242, 1), (32770, 1),
+                                       (13312, 2), (16384, 2), (16898, 2), (33794, 2)])
 def test_one_step_against_fp64(N, posmode, tensor):
     sus = make_single(N // 2, 240.0 * (N / 4096) ** (1 / 3), 1)
     got = _displacements(sus.params, sus.X, sus.phi, 1, precision="fp32c", tensor=tensor,
@@ -51,7 +51,7 @@ def test_replayed_and_split_steps_give_the_same_bits(integrator):
     assert np.array_equal(a, b) and np.array_equal(a, s.get_state()[0].cpu().numpy() - sus.X)
 
 
-@pytest.mark.parametrize("N,posmode,side,rmin", [(8192, 1, 170.0, 1.6), (8194, 1, 90.0, 1.8), (8702, 2, 100.0, 1.6)])
+@pytest.mark.parametrize("N,posmode,side,rmin", [(4096, 1, 120.0, 1.6), (4098, 2, 120.0, 1.6), (8192, 1, 170.0, 1.6), (8194, 1, 90.0, 1.8), (8702, 2, 100.0, 1.6)])
 def test_steric_contacts_against_fp64(N, posmode, side, rmin):
     """Contacts across chunks and blocks, dense enough that several lie in one
     group of steps; the FP64 form sums every pair."""
