@@ -1915,10 +1915,10 @@ struct Range64 {
         return (h | lo_word(x)) == 0 || h >= kFrLo;
     }
 };
-/* ir = 1/sqrt(x) as the plain expression rounds it, and y = 1/x (rounded but
+/* s = sqrt(x) and ir = 1/s as the plain expressions round them, and y = 1/x (rounded but
  * for rare last-bit cases) for div_exact; ones is raised to 0xffffffff where
  * the short forms do not hold (s or x with an all-ones low word) */
-__device__ __forceinline__ void rcp_sqrt_exact(double x, double& ir, double& y, unsigned& ones) {
+__device__ __forceinline__ void rcp_sqrt_exact(double x, double& s, double& ir, double& y, unsigned& ones) {
     const double v = __builtin_amdgcn_rsq(x);
     double g = x * v;
     double h = v * 0.5;
@@ -1928,7 +1928,7 @@ __device__ __forceinline__ void rcp_sqrt_exact(double x, double& ir, double& y, 
     double q = __builtin_fma(-g, g, x);
     g = __builtin_fma(q, h, g);
     q = __builtin_fma(-g, g, x);
-    const double s = __builtin_fma(q, h, g);
+    s = __builtin_fma(q, h, g);
     ones = max(ones, max(lo_word(s), lo_word(x)));
     const double h2 = h + h;
     y = h2 * h2;
@@ -2443,7 +2443,8 @@ __global__ __launch_bounds__(64 * (NP + 1)) void k_pairs_f64w(Dev d, Epi e, int 
                 fr[u][q] = (rx[u][q] * Fx + ry[u][q] * Fy) + rz[u][q] * Fz;
                 rg.r2(r2[u][q]);
                 rg.fr(fr[u][q]);
-                rcp_sqrt_exact(r2[u][q], ir[u][q], iy[u][q], rg.ones);
+                double s;
+                rcp_sqrt_exact(r2[u][q], s, ir[u][q], iy[u][q], rg.ones);
             }
         }
         bool ok = rg.ok();
@@ -2734,11 +2735,21 @@ __device__ __forceinline__ void combine_level_shfl(float v[6], int sh) {
 /* FP64 (the plain sum, bitwise that of the sequential oracle): X, R, Y, F
  * and the pair sums in LDS. Per stage: the terms of a chunk of source
  * columns are evaluated in parallel into an LDS matrix, then every
- * (target, component) thread adds its row of the chunk in ascending j;
- * the closing (velocity, stage update, next stage position) takes one
- * thread per sphere component, the next stage's spring forces one thread
- * per sphere (both threads of a dumbbell evaluate them from the same
- * inputs, so they agree bit for bit). */
+ * (target, component) thread adds its row of the chunk in ascending j and
+ * closes it (velocity, stage update, next stage position); then one thread
+ * per sphere forms the next stage's spring force (both threads of a dumbbell
+ * evaluate them from the same inputs, so they agree bit for bit).
+ * What bounds it is the length of that chain, of which four barriers, two
+ * square roots and three divisions in a row were the larger part. Up to 16
+ * spheres no thread has more than one pair: it forms its source's spring force
+ * itself, next to the pair's separation, so both square roots and the
+ * reciprocals run side by side (rcp_sqrt_exact), and a stage has two barriers.
+ * With more, a thread has several pairs one after another and would form a
+ * spring force for each, so they keep the springs' own phase. RK4 step, before
+ * and after: 2 spheres 4.04 and 3.88 us, 6 4.62 and 3.76, 14
+ * 4.95 and 4.15, 16 4.35 and 3.80 (RPY 5.10 and 4.48); Heun with noise, 16
+ * spheres: 3.92 and 2.44 us (the noise, the same in both stages, is formed in
+ * the first). */
 template <int RPY, int INTEG>
 __global__ __launch_bounds__(RES_T) void k_resident(Dev d, Epi e, long long step0, int nsteps, double st0,
                                                     double ct0) {
@@ -2772,8 +2783,13 @@ __global__ __launch_bounds__(RES_T) void k_resident(Dev d, Epi e, long long step
         X[q] = v;
         Y[q] = v;
     }
+    /* one: at most one pair per thread, (pi, pj), which forms sphere pj's
+     * spring force itself; else thread tid < n forms sphere tid's */
+    const bool one = n * n <= T;
+    const int pi = one ? tid / n : 0, pj = one ? tid - pi * n : tid;
+    const bool springs = tid < (one ? n * n : n);
     double2 tp = make_double2(0.0, 0.0);
-    if (tid < n) tp = d.phitrig[(ioff >> 1) + (tid >> 1)];
+    if (springs) tp = d.phitrig[(ioff >> 1) + (pj >> 1)];
     int bad = 0;
     /* the step table's row index in a vector register: its loads are then
      * vector loads, which the LDS-only barriers do not wait for */
@@ -2781,7 +2797,7 @@ __global__ __launch_bounds__(RES_T) void k_resident(Dev d, Epi e, long long step
     asm volatile("" : "+v"(row));
     double tb[8], nb[8];
     for (int q = 0; q < 8; ++q) tb[q] = nb[q] = 0.0;
-    if (tid < n)
+    if (springs)
         for (int q = 0; q < 8; ++q) tb[q] = d.tab[row * 8 + q];
     __syncthreads();
 
@@ -2798,29 +2814,92 @@ __global__ __launch_bounds__(RES_T) void k_resident(Dev d, Epi e, long long step
         }
         lds_barrier();
     };
-    forces(st0, ct0);
+    auto store_term = [&](int o, const double t[3], const double tq[3]) {
+        const int m = n * cs; /* component stride */
+        for (int a = 0; a < 3; ++a) {
+            Tm[a * m + o] = t[a];
+            if (RPY) Tb[a * m + o] = tq[a];
+        }
+    };
+    /* the spring force of sphere pj, kept by its own pair's thread, and the
+     * term of the pair (pi, pj), their square roots and divisions together by
+     * the short forms where those hold */
+    auto pair_of_one = [&](double st, double ct) {
+        const int i0 = pj & ~1;
+        double y0[3], y1[3], r[3], Fj[3], F0[3], t[3] = {0.0, 0.0, 0.0}, tq[3] = {0.0, 0.0, 0.0};
+        for (int a = 0; a < 3; ++a) {
+            y0[a] = Y[a * n + i0];
+            y1[a] = Y[a * n + i0 + 1];
+            r[a] = Y[a * n + pi] - ((pj & 1) ? y1[a] : y0[a]);
+        }
+        const double nv[3] = {y1[0] - y0[0], y1[1] - y0[1], y1[2] - y0[2]};
+        const double n2 = (nv[0] * nv[0] + nv[1] * nv[1]) + nv[2] * nv[2];
+        const bool self = pi == pj;
+        const double r2 = self ? 1.0 : (r[0] * r[0] + r[1] * r[1]) + r[2] * r[2];
+        Range64 rg;
+        double dd, id, iy, rr, ir, iz;
+        rcp_sqrt_exact(n2, dd, id, iy, rg.ones);
+        rcp_sqrt_exact(r2, rr, ir, iz, rg.ones);
+        const double pull = -c.k * (dd - (c.ell + c.lam * (st * tp.y + ct * tp.x)));
+        const double cc1 = div_exact(pull, dd, id);
+        for (int a = 0; a < 3; ++a) Fj[a] = (pj & 1) ? cc1 * nv[a] : -(cc1 * nv[a]);
+        const double fr = (r[0] * Fj[0] + r[1] * Fj[1]) + r[2] * Fj[2];
+        rg.r2(n2);
+        rg.r2(r2);
+        rg.fr(pull);
+        rg.fr(fr);
+        if (__builtin_expect(rg.ok() && (!rg.small_fr() || (Range64::fr_fits(pull) && Range64::fr_fits(fr))), 1)) {
+            const double tt = div_exact(fr, r2, iz);
+            for (int a = 0; a < 3; ++a) t[a] = ir * (Fj[a] + tt * r[a]);
+            if (RPY) {
+                const double ir3 = div_exact(ir, r2, iz), t3 = 3.0 * tt;
+                for (int a = 0; a < 3; ++a) tq[a] = ir3 * (Fj[a] - t3 * r[a]);
+            }
+        } else {
+            double f1[3];
+            spring_forces(c, y0, y1, tp.x, tp.y, st, ct, F0, f1);
+            for (int a = 0; a < 3; ++a) Fj[a] = (pj & 1) ? f1[a] : F0[a];
+            if (r2 != 0.0) {
+                oseen_term64(r, Fj, t);
+                if (RPY) rpy_term64(r, Fj, tq);
+            } else {
+                bad = 1;
+            }
+        }
+        if (self) {
+            for (int a = 0; a < 3; ++a) {
+                F[a * n + pj] = Fj[a];
+                t[a] = tq[a] = 0.0;
+            }
+        }
+        store_term(pi * cs + pj, t, tq);
+    };
+    double noise[2] = {0.0, 0.0}; /* of this thread's at most two rows */
+    static_assert(3 * RES_MAX64 <= 2 * RES_T, "rows per thread");
+    double fst = st0, fct = ct0; /* the time of the next forces */
+    if (!one) forces(fst, fct);
 
-    auto stage_pass = [&](auto stage_c, long long step) {
+    auto stage_pass = [&](auto one_c, auto stage_c, long long step) {
+        constexpr bool ONE = decltype(one_c)::value;
         constexpr int stage = decltype(stage_c)::value;
         for (int j0 = 0; j0 < n; j0 += cc) {
             const int nc = min(cc, n - j0);
-            for (int p = tid; p < n * nc; p += T) {
-                const int i = p / nc, jj = p - i * nc, j = j0 + jj;
-                const int o = i * cs + jj;
-                const int m = n * cs; /* component stride */
-                const double r[3] = {Y[i] - Y[j], Y[n + i] - Y[n + j], Y[2 * n + i] - Y[2 * n + j]};
-                const double r2 = (r[0] * r[0] + r[1] * r[1]) + r[2] * r[2];
-                double t[3] = {0.0, 0.0, 0.0}, tq[3] = {0.0, 0.0, 0.0};
-                if (j != i && r2 != 0.0) {
-                    const double Fj[3] = {F[j], F[n + j], F[2 * n + j]};
-                    oseen_term64(r, Fj, t);
-                    if (RPY) rpy_term64(r, Fj, tq);
-                } else if (j != i) {
-                    bad = 1;
-                }
-                for (int a = 0; a < 3; ++a) {
-                    Tm[a * m + o] = t[a];
-                    if (RPY) Tb[a * m + o] = tq[a];
+            if constexpr (ONE) {
+                if (springs) pair_of_one(fst, fct);
+            } else {
+                for (int p = tid; p < n * nc; p += T) {
+                    const int i = p / nc, jj = p - i * nc, j = j0 + jj;
+                    const double r[3] = {Y[i] - Y[j], Y[n + i] - Y[n + j], Y[2 * n + i] - Y[2 * n + j]};
+                    const double r2 = (r[0] * r[0] + r[1] * r[1]) + r[2] * r[2];
+                    double t[3] = {0.0, 0.0, 0.0}, tq[3] = {0.0, 0.0, 0.0};
+                    if (j != i && r2 != 0.0) {
+                        const double Fj[3] = {F[j], F[n + j], F[2 * n + j]};
+                        oseen_term64(r, Fj, t);
+                        if (RPY) rpy_term64(r, Fj, tq);
+                    } else if (j != i) {
+                        bad = 1;
+                    }
+                    store_term(i * cs + jj, t, tq);
                 }
             }
             lds_barrier();
@@ -2849,43 +2928,76 @@ __global__ __launch_bounds__(RES_T) void k_resident(Dev d, Epi e, long long step
                         if (RPY) bcc = bcc + w[u];
                     }
                 }
-                for (; jb < nc; ++jb) {
-                    acc = acc + row[jb];
-                    if (RPY) bcc = bcc + rowb[jb];
+                if constexpr (ONE) { /* the rest together too, +0.0 past the end */
+                    double v[8], w[8];
+                    if (jb < nc) {
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) {
+                            const int at = min(jb + u, nc - 1);
+                            v[u] = row[at];
+                            w[u] = RPY ? rowb[at] : 0.0;
+                        }
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) {
+                            acc = acc + (jb + u < nc ? v[u] : 0.0);
+                            if (RPY) bcc = bcc + (jb + u < nc ? w[u] : 0.0);
+                        }
+                    }
+                } else {
+                    for (; jb < nc; ++jb) {
+                        acc = acc + row[jb];
+                        if (RPY) bcc = bcc + rowb[jb];
+                    }
                 }
                 Acc[q] = acc;
                 if (RPY) Bcc[q] = bcc;
             }
-            lds_barrier();
+            if (!ONE && j0 + cc < n) lds_barrier(); /* before the next chunk's terms */
         }
-        /* closing, one thread per (component, sphere) */
-        for (int q = tid; q < 3 * n; q += T) {
+        /* closing: each thread the (component, sphere) rows that it summed */
+        for (int q = tid, w = 0; q < 3 * n; q += T, ++w) {
             const int a = (q >= n) + (q >= 2 * n), i = q - a * n, o = q;
             double k = c.cs * F[o] + c.co * Acc[o];
             if (RPY) k = k + c.cr * Bcc[o];
             if (!isfinite(k)) bad = 1;
-            const double nz = INTEG == 2 ? c.g * gauss_component(c.seed, ioff + i, step, a) : 0.0;
+            double nz = 0.0;
+            if (INTEG == 2) { /* a step's two stages add the same noise */
+                if (stage == 0) {
+                    nz = c.g * gauss_component(c.seed, ioff + i, step, a);
+                    noise[w ? 1 : 0] = nz;
+                } else {
+                    nz = w ? noise[1] : noise[0];
+                }
+            }
             double x = X[o], r = R[o];
             Y[o] = res_update(c, INTEG == 0 ? 0 : 1, stage, NST, k, x, r, nz);
             X[o] = x;
             R[o] = r;
         }
         lds_barrier();
-        forces(tb[2 * stage], tb[2 * stage + 1]);
+        fst = tb[2 * stage];
+        fct = tb[2 * stage + 1];
+        if (!ONE) forces(fst, fct);
     };
-    for (int sn = 0; sn < nsteps; ++sn) {
-        const long long step = step0 + sn;
-        row = row + 1 == d.ring ? 0 : row + 1;
-        if (tid < n)
-            for (int q = 0; q < 8; ++q) nb[q] = d.tab[row * 8 + q];
-        stage_pass(std::integral_constant<int, 0>{}, step);
-        stage_pass(std::integral_constant<int, 1>{}, step);
-        if constexpr (NST == 4) {
-            stage_pass(std::integral_constant<int, 2>{}, step);
-            stage_pass(std::integral_constant<int, 3>{}, step);
+    auto run = [&](auto one_c) {
+        for (int sn = 0; sn < nsteps; ++sn) {
+            const long long step = step0 + sn;
+            row = row + 1 == d.ring ? 0 : row + 1;
+            if (springs)
+                for (int q = 0; q < 8; ++q) nb[q] = d.tab[row * 8 + q];
+            stage_pass(one_c, std::integral_constant<int, 0>{}, step);
+            stage_pass(one_c, std::integral_constant<int, 1>{}, step);
+            if constexpr (NST == 4) {
+                stage_pass(one_c, std::integral_constant<int, 2>{}, step);
+                stage_pass(one_c, std::integral_constant<int, 3>{}, step);
+            }
+            for (int q = 0; q < 8; ++q) tb[q] = nb[q];
         }
-        for (int q = 0; q < 8; ++q) tb[q] = nb[q];
-    }
+    };
+    if (one)
+        run(std::integral_constant<bool, true>{});
+    else
+        run(std::integral_constant<bool, false>{});
     for (int q = tid; q < 3 * n; q += T) {
         const int a = q / n, i = q - a * n;
         d.X[a * N + ioff + i] = X[q];
