@@ -105,6 +105,109 @@ __device__ int steric_sum(const Coef& c, int i, int j0, int j1, Get get, double 
     return bad;
 }
 
+/* The full steric sums of a dumbbell's two spheres, by one thread (IT = 0,
+ * steric_sum) or by a wave for its IT spheres, IT / 2 dumbbells of one system
+ * from s0 on: the lanes test 64 sources at a time, each against every sphere,
+ * on the high words of r^2 and rc^2 (an FP64 compare costs as much as the
+ * separation), and where one may be in reach the wave goes over the lanes that
+ * pass in order, so every sum is steric_sum's, bit for bit. What bounds it is
+ * the FP64 rate: 8 operations per sphere and 64 sources.
+ * Lane q adds up sphere q; the lanes 2m then hold dumbbell s0 + m. */
+template <int IT>
+__device__ __forceinline__ int steric_dumbbell(const Dev& d, int& s0) {
+    if (IT == 0) {
+        s0 = blockIdx.x * blockDim.x + threadIdx.x;
+        return s0 < d.Stot ? s0 : -1;
+    }
+    const int lane = threadIdx.x & 63;
+    s0 = __builtin_amdgcn_readfirstlane((blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * (IT / 2));
+    return (lane & 1) == 0 && lane < IT && s0 + (lane >> 1) < d.Stot ? s0 + (lane >> 1) : -1;
+}
+__device__ __forceinline__ double read_lane(double v, int l) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, l), hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), l);
+    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+}
+/* adds the steric forces of dumbbell s (from steric_dumbbell) to f0 and f1 */
+template <int IT, class Get>
+__device__ __forceinline__ int add_steric(const Dev& d, const Coef& c, int s, int s0, Get get, double f0[3],
+                                          double f1[3]) {
+    int bad = 0;
+    if (IT == 0) {
+        const int b = d.dsys[s], j0 = d.sys_off[b], j1 = d.sys_off[b + 1];
+        double acc[3];
+        int any;
+        bad |= steric_sum(c, 2 * s, j0, j1, get, acc, &any);
+        if (any)
+            for (int a = 0; a < 3; ++a) f0[a] = f0[a] + acc[a];
+        bad |= steric_sum(c, 2 * s + 1, j0, j1, get, acc, &any);
+        if (any)
+            for (int a = 0; a < 3; ++a) f1[a] = f1[a] + acc[a];
+        return bad;
+    }
+    if (s0 >= d.Stot) return 0;
+    constexpr int NQ = IT ? IT : 1;
+    const int lane = threadIdx.x & 63;
+    const int b = d.dsys[s0], j0 = d.sys_off[b], j1 = d.sys_off[b + 1];
+    const int nq = min(NQ, 2 * (d.Stot - s0));
+    const double rc2 = c.rc * c.rc;
+    const unsigned reach = (unsigned)(__builtin_bit_cast(unsigned long long, rc2) >> 32);
+    double xi[NQ][3];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) get(2 * s0 + min(q, nq - 1), xi[q]);
+    double acc[3] = {0.0, 0.0, 0.0};
+    bool any = false;
+    double xj[3], xn[3];
+    get(min(j0 + lane, j1 - 1), xn);
+    for (int jt = j0; jt < j1; jt += 64) {
+        for (int a = 0; a < 3; ++a) xj[a] = xn[a];
+        if (jt + 64 < j1) get(min(jt + 64 + lane, j1 - 1), xn);
+        unsigned lo = 0xffffffffu, hi = 0; /* of the high words; NaN's are above infinity's */
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const double rx = xi[q][0] - xj[0], ry = xi[q][1] - xj[1], rz = xi[q][2] - xj[2];
+            const double r2 = (rx * rx + ry * ry) + rz * rz;
+            const unsigned h = (unsigned)(__builtin_bit_cast(unsigned long long, r2) >> 32) & 0x7fffffffu;
+            lo = min(lo, h);
+            hi = max(hi, h);
+        }
+        if (!__any(lo <= reach || hi >= 0x7ff00000u)) continue;
+#pragma unroll 1
+        for (int q = 0; q < nq; ++q) {
+            double y[3];
+            get(2 * s0 + q, y);
+            const double tx = y[0] - xj[0], ty = y[1] - xj[1], tz = y[2] - xj[2];
+            const double t2 = (tx * tx + ty * ty) + tz * tz;
+            const int j = jt + lane;
+            unsigned long long in = __ballot(j < j1 && j != 2 * s0 + q && !(t2 >= rc2));
+            while (in) {
+                const int l = __builtin_ctzll(in);
+                in &= in - 1;
+                const double rx = read_lane(tx, l), ry = read_lane(ty, l), rz = read_lane(tz, l);
+                const double r2 = read_lane(t2, l);
+                if (r2 == 0.0) {
+                    bad = 1;
+                    continue;
+                }
+                const double r = sqrt(r2);
+                const double cc = c.ks * (c.rc - r) / r;
+                if (lane == q) {
+                    acc[0] = acc[0] + cc * rx;
+                    acc[1] = acc[1] + cc * ry;
+                    acc[2] = acc[2] + cc * rz;
+                    any = true;
+                }
+            }
+        }
+    }
+    for (int a = 0; a < 3; ++a) {
+        const double other = __shfl_xor(acc[a], 1);
+        if (any) f0[a] = f0[a] + acc[a];
+        if (__shfl_xor((int)any, 1)) f1[a] = f1[a] + other;
+    }
+    return bad;
+}
+
 __device__ __forceinline__ void split_f32(double v, float& hi, float& lo) {
     hi = (float)v;
     lo = (float)(v - (double)hi);
@@ -356,35 +459,28 @@ __global__ void k_clear_counts(Dev d) {
 }
 
 /* pack from the state at time (st, ct); spring (+ steric) forces */
-__global__ void k_pack_state(Dev d, Coef c, int prec, double st, double ct) {
-    int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= d.Stot) return;
+template <int IT>
+__global__ __launch_bounds__(256) void k_pack_state(Dev d, Coef c, int prec, double st, double ct) {
+    int s0;
+    const int s = steric_dumbbell<IT>(d, s0);
+    if (IT == 0 && s < 0) return;
     const int N = d.Ntot;
-    const int i0 = 2 * s;
+    const int i0 = 2 * max(s, 0);
     double y0[3], y1[3], f0[3], f1[3];
     for (int a = 0; a < 3; ++a) {
         y0[a] = d.X[a * N + i0];
         y1[a] = d.X[a * N + i0 + 1];
     }
-    double2 tp = d.phitrig[s];
+    double2 tp = d.phitrig[max(s, 0)];
     spring_forces(c, y0, y1, tp.x, tp.y, st, ct, f0, f1);
     if (c.ks != 0.0) {
-        int b = d.dsys[s];
-        int j0 = d.sys_off[b], j1 = d.sys_off[b + 1];
         auto get = [&](int j, double x[3]) {
             x[0] = d.X[j];
             x[1] = d.X[N + j];
             x[2] = d.X[2 * N + j];
         };
-        double acc[3];
-        int any, bad = 0;
-        bad |= steric_sum(c, i0, j0, j1, get, acc, &any);
-        if (any)
-            for (int a = 0; a < 3; ++a) f0[a] = f0[a] + acc[a];
-        bad |= steric_sum(c, i0 + 1, j0, j1, get, acc, &any);
-        if (any)
-            for (int a = 0; a < 3; ++a) f1[a] = f1[a] + acc[a];
-        if (bad) atomicOr(&d.ctl->flag, FLAG_NONFINITE);
+        if (add_steric<IT>(d, c, s, s0, get, f0, f1)) atomicOr(&d.ctl->flag, FLAG_NONFINITE);
+        if (s < 0) return;
         /* stage positions (for the displacement check) and empty candidate
          * lists for the first pair sum */
         for (int a = 0; a < 3; ++a) {
@@ -416,35 +512,28 @@ __global__ void k_pack_apply(Dev d, Coef c, int prec, const double* __restrict__
 }
 
 /* spring + steric forces at caller positions, row-major output */
-__global__ void k_forces(Dev d, Coef c, const double* __restrict__ Xa, double st, double ct,
-                         double* __restrict__ Fa) {
-    int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= d.Stot) return;
-    const int i0 = 2 * s;
+template <int IT>
+__global__ __launch_bounds__(256) void k_forces(Dev d, Coef c, const double* __restrict__ Xa, double st, double ct,
+                                                double* __restrict__ Fa) {
+    int s0;
+    const int s = steric_dumbbell<IT>(d, s0);
+    if (IT == 0 && s < 0) return;
+    const int i0 = 2 * max(s, 0);
     double y0[3], y1[3], f0[3], f1[3];
     for (int a = 0; a < 3; ++a) {
         y0[a] = Xa[3 * i0 + a];
         y1[a] = Xa[3 * i0 + 3 + a];
     }
-    double2 tp = d.phitrig[s];
+    double2 tp = d.phitrig[max(s, 0)];
     spring_forces(c, y0, y1, tp.x, tp.y, st, ct, f0, f1);
     if (c.ks != 0.0) {
-        int b = d.dsys[s];
-        int j0 = d.sys_off[b], j1 = d.sys_off[b + 1];
         auto get = [&](int j, double x[3]) {
             x[0] = Xa[3 * j];
             x[1] = Xa[3 * j + 1];
             x[2] = Xa[3 * j + 2];
         };
-        double acc[3];
-        int any, bad = 0;
-        bad |= steric_sum(c, i0, j0, j1, get, acc, &any);
-        if (any)
-            for (int a = 0; a < 3; ++a) f0[a] = f0[a] + acc[a];
-        bad |= steric_sum(c, i0 + 1, j0, j1, get, acc, &any);
-        if (any)
-            for (int a = 0; a < 3; ++a) f1[a] = f1[a] + acc[a];
-        if (bad) atomicOr(&d.ctl->flag, FLAG_NONFINITE);
+        if (add_steric<IT>(d, c, s, s0, get, f0, f1)) atomicOr(&d.ctl->flag, FLAG_NONFINITE);
+        if (s < 0) return;
     }
     for (int a = 0; a < 3; ++a) {
         Fa[3 * i0 + a] = f0[a];
@@ -2551,12 +2640,14 @@ __device__ int steric_list(const Dev& d, const Coef& c, int i, double acc[3], in
 }
 
 /* steric forces at the stage positions Y, then the pack: from the candidate
- * lists when the pair kernel records them, else by the full ascending sum */
-__global__ void k_steric_pack(Dev d, Coef c, int prec) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= d.Stot) return;
+ * lists when the pair kernel records them (LIST), else by the full sum */
+template <int LIST, int IT>
+__global__ __launch_bounds__(256) void k_steric_pack(Dev d, Coef c, int prec) {
+    int s0;
+    const int s = steric_dumbbell<IT>(d, s0);
+    if (IT == 0 && s < 0) return;
     const int N = d.Ntot;
-    const int i0 = 2 * s;
+    const int i0 = 2 * max(s, 0);
     double y0[3], y1[3], f0[3], f1[3];
     for (int a = 0; a < 3; ++a) {
         y0[a] = d.Y[a * N + i0];
@@ -2564,9 +2655,10 @@ __global__ void k_steric_pack(Dev d, Coef c, int prec) {
         f0[a] = d.Fs[a * N + i0];
         f1[a] = d.Fs[a * N + i0 + 1];
     }
-    double acc[3];
-    int any, bad = 0;
-    if (d.nbr_cnt) {
+    int bad = 0;
+    if (LIST) {
+        double acc[3];
+        int any;
         bad |= steric_list(d, c, i0, acc, &any);
         if (any)
             for (int a = 0; a < 3; ++a) f0[a] = f0[a] + acc[a];
@@ -2574,21 +2666,15 @@ __global__ void k_steric_pack(Dev d, Coef c, int prec) {
         if (any)
             for (int a = 0; a < 3; ++a) f1[a] = f1[a] + acc[a];
     } else {
-        const int b = d.dsys[s];
-        const int j0 = d.sys_off[b], j1 = d.sys_off[b + 1];
         auto get = [&](int j, double x[3]) {
             x[0] = d.Y[j];
             x[1] = d.Y[N + j];
             x[2] = d.Y[2 * N + j];
         };
-        bad |= steric_sum(c, i0, j0, j1, get, acc, &any);
-        if (any)
-            for (int a = 0; a < 3; ++a) f0[a] = f0[a] + acc[a];
-        bad |= steric_sum(c, i0 + 1, j0, j1, get, acc, &any);
-        if (any)
-            for (int a = 0; a < 3; ++a) f1[a] = f1[a] + acc[a];
+        bad |= add_steric<IT>(d, c, s, s0, get, f0, f1);
     }
     if (bad) atomicOr(&d.ctl->flag, FLAG_NONFINITE);
+    if (s < 0) return;
     store_pack(d, c, prec, i0, y0, y1, f0, f1, 1);
 }
 
@@ -3218,8 +3304,32 @@ hipError_t launch_state_out(const Dev& d, double* Xa, hipStream_t s) {
     return hipGetLastError();
 }
 
+/* Spheres per wave in the full steric sums (add_steric), 0 where a thread
+ * takes a dumbbell: the thread's chain is 0.28 us per sphere of its system,
+ * the wave's work 0.0006 us per dumbbell, so from about 1000 systems on the
+ * threads are faster, whatever the systems' size (ad_forces, us, thread and
+ * wave: 512 systems of 8 spheres 10 and 10, of 200 73 and 35; 8192 of 8 13 and
+ * 16; 30000 of 4 10 and 26; a single one of 4096 spheres 1174 and 19). Eight
+ * spheres share a wave's loads of a source where that leaves enough waves:
+ * 4096 spheres 28 us (two: 19), 16384 119 (145), 65536 1.49 ms (2.28; by
+ * threads 18.8). */
+static int steric_spheres(const Dev& d, const Coef& c) {
+    if (c.ks == 0.0 || d.nsys >= 1024) return 0;
+    return d.nsys == 1 && d.Ntot >= 16384 ? 8 : 2;
+}
+static dim3 steric_grid(const Dev& d, int it) {
+    return it ? blocks_for(d.Stot, 4 * (it / 2)) : blocks_for(d.Stot, 128);
+}
+
 hipError_t launch_pack_state(const Dev& d, const Coef& c, int prec, double st, double ct, hipStream_t s) {
-    hipLaunchKernelGGL(k_pack_state, blocks_for(d.Stot, 128), dim3(128), 0, s, d, c, prec, st, ct);
+    const int it = steric_spheres(d, c);
+    const dim3 g = steric_grid(d, it), t(it ? 256 : 128);
+    if (it == 0)
+        hipLaunchKernelGGL(k_pack_state<0>, g, t, 0, s, d, c, prec, st, ct);
+    else if (it == 2)
+        hipLaunchKernelGGL(k_pack_state<2>, g, t, 0, s, d, c, prec, st, ct);
+    else
+        hipLaunchKernelGGL(k_pack_state<8>, g, t, 0, s, d, c, prec, st, ct);
     return hipGetLastError();
 }
 
@@ -3231,7 +3341,14 @@ hipError_t launch_pack_apply(const Dev& d, const Coef& c, int prec, const double
 
 hipError_t launch_forces(const Dev& d, const Coef& c, const double* Xa, double st, double ct, double* Fa,
                          hipStream_t s) {
-    hipLaunchKernelGGL(k_forces, blocks_for(d.Stot, 128), dim3(128), 0, s, d, c, Xa, st, ct, Fa);
+    const int it = steric_spheres(d, c);
+    const dim3 g = steric_grid(d, it), t(it ? 256 : 128);
+    if (it == 0)
+        hipLaunchKernelGGL(k_forces<0>, g, t, 0, s, d, c, Xa, st, ct, Fa);
+    else if (it == 2)
+        hipLaunchKernelGGL(k_forces<2>, g, t, 0, s, d, c, Xa, st, ct, Fa);
+    else
+        hipLaunchKernelGGL(k_forces<8>, g, t, 0, s, d, c, Xa, st, ct, Fa);
     return hipGetLastError();
 }
 
@@ -3549,7 +3666,16 @@ hipError_t launch_epilogue(const Dev& d, const Epi& e, hipStream_t s) {
 }
 
 hipError_t launch_steric_pack(const Dev& d, const Coef& c, int prec, hipStream_t s) {
-    hipLaunchKernelGGL(k_steric_pack, blocks_for(d.Stot, 128), dim3(128), 0, s, d, c, prec);
+    const int it = d.nbr_cnt ? 0 : steric_spheres(d, c);
+    const dim3 g = steric_grid(d, it), t(it ? 256 : 128);
+    if (d.nbr_cnt)
+        hipLaunchKernelGGL((k_steric_pack<1, 0>), g, t, 0, s, d, c, prec);
+    else if (it == 0)
+        hipLaunchKernelGGL((k_steric_pack<0, 0>), g, t, 0, s, d, c, prec);
+    else if (it == 2)
+        hipLaunchKernelGGL((k_steric_pack<0, 2>), g, t, 0, s, d, c, prec);
+    else
+        hipLaunchKernelGGL((k_steric_pack<0, 8>), g, t, 0, s, d, c, prec);
     return hipGetLastError();
 }
 
