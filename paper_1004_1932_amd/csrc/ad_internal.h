@@ -152,6 +152,18 @@ __device__ __forceinline__ void advance_step(const Dev& d, const Epi& e, long lo
     if (e.stage == e.nst - 1) d.ctl->slot[0] = step + 1;
 }
 
+/* Append source j to the steric candidate list of target i. (Inline, and by
+ * pointers: as a call that took the Dev, every wave first copied it to scratch,
+ * 17 KB: 30000 dumbbells 365 us per RK4 step, 106 this way.) */
+__device__ __forceinline__ void append(int* cnt, int* idx, int* flag, int i, int j) {
+    /* unsigned test: a count outside [0, NBR_CAP) never becomes an index */
+    const unsigned k = (unsigned)atomicAdd(&cnt[i], 1);
+    if (k < (unsigned)NBR_CAP)
+        idx[i * NBR_CAP + (int)k] = j;
+    else
+        atomicOr(flag, FLAG_NBR_FULL);
+}
+
 /* x[q] = 1/sqrt(x[q]) (v_rsq_f32) for four terms together, set apart from the
  * instructions around them by a scalar one on each side.
  * A SIMD issues vector instructions of two waves at once (measured: 1.7 to 1.9
@@ -253,10 +265,10 @@ hipError_t launch_pairs_sym(const Dev& d, const Epi& e, const Shape& sh, hipStre
  * pays for partial sums at both ends of a pair. us per RK4 step against the
  * ordered pair kernel: hi/lo 8192 spheres 195 (190), 9000 226 (242), 12000 325
  * (335); single-float 12000 295 (301), 13000 335 (334), 14000 353 (381), 15002
- * 389 (426); steric, hi/lo 3000 128 (128), 4096 135 (153), 6000 171 (206);
- * steric, single-float 3000 118 (171), 5000 136 (192). */
+ * 389 (426); steric, hi/lo 7000 198 (207), 8192 239 (226), 10000 302 (336),
+ * 16384 571 (749); steric, single-float 8300 217 (217), 12000 328 (352). */
 inline bool sym_takes(int N, int hilo, int steric) {
-    return N >= (steric ? 4096 : hilo ? 8704 : 13312);
+    return N >= (steric || hilo ? 8704 : 13312);
 }
 /* spheres per block: work-groups of 4 or 8 waves, 128 spheres per wave (the
  * larger block halves the partial sums of the largest systems) */

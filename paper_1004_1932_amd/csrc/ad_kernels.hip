@@ -797,18 +797,6 @@ __device__ __forceinline__ void load_tile_entry(const Dev& d, int t0, int jend, 
     }
 }
 
-/* append source j to the steric candidate list of target i (i < iend) */
-__device__ __noinline__ void add_candidate(const Dev& d, int i, int iend, int j) {
-    if (i >= iend) return;
-    /* unsigned test: a count outside [0, NBR_CAP) never becomes an index */
-    const unsigned k = (unsigned)atomicAdd(&d.nbr_cnt[i], 1);
-    if (k < (unsigned)NBR_CAP)
-        d.nbr_idx[i * NBR_CAP + (int)k] = j;
-    else
-        atomicOr(&d.ctl->flag, FLAG_NBR_FULL);
-}
-
-
 /* FP32C pair sum. A work-group of WG threads is WI x WJ waves: WI waves own
  * different target spheres (IPL consecutive spheres per lane), and the WJ
  * waves that share the same targets take interleaved parts of every j-tile.
@@ -923,7 +911,8 @@ __global__ __launch_bounds__(WG) void k_pairs_f32c(Dev d, Epi e, int mode) {
                         }
                         ir[q][u] = __builtin_fmaf(rz[q][u], rz[q][u],
                                                   __builtin_fmaf(ry[q][u], ry[q][u], rx[q][u] * rx[q][u]));
-                        if (STERIC && ir[q][u] < d.list_r2) add_candidate(d, ib + q, iend, t0 + jj + u);
+                        if (STERIC && ir[q][u] < d.list_r2 && ib + q < iend)
+                            append(d.nbr_cnt, d.nbr_idx, &d.ctl->flag, ib + q, t0 + jj + u);
                     }
                 }
 #pragma unroll
@@ -954,7 +943,8 @@ __global__ __launch_bounds__(WG) void k_pairs_f32c(Dev d, Epi e, int mode) {
                         rz = hz[q] - Aj.z;
                     }
                     float r2 = __builtin_fmaf(rz, rz, __builtin_fmaf(ry, ry, rx * rx));
-                    if (STERIC && r2 < d.list_r2 && t0 + jj != ib + q) add_candidate(d, ib + q, iend, t0 + jj);
+                    if (STERIC && r2 < d.list_r2 && t0 + jj != ib + q && ib + q < iend)
+                        append(d.nbr_cnt, d.nbr_idx, &d.ctl->flag, ib + q, t0 + jj);
                     float ir = (dj == dq[q]) ? 0.f : __builtin_amdgcn_rsqf(r2);
                     pair_term<RPY>(ir, rx, ry, rz, Aj.w, Bj.w, Fz, crr, px[q], py[q], pz[q]);
                 }

@@ -75,15 +75,6 @@ __device__ __forceinline__ void rsq_move(float x[2], float& qx, float& qy, float
 }
 #undef AD_MOVE3
 
-/* append source j to the steric candidate list of target i */
-__device__ __forceinline__ void append(int* cnt, int* idx, int* flag, int i, int j) {
-    const unsigned k = (unsigned)atomicAdd(&cnt[i], 1);
-    if (k < (unsigned)NBR_CAP)
-        idx[i * NBR_CAP + (int)k] = j;
-    else
-        atomicOr(flag, FLAG_NBR_FULL);
-}
-
 /* What both terms of a pair share. */
 template <int RPY>
 struct Pair {

@@ -51,7 +51,8 @@ def test_replayed_and_split_steps_give_the_same_bits(integrator):
     assert np.array_equal(a, b) and np.array_equal(a, s.get_state()[0].cpu().numpy() - sus.X)
 
 
-@pytest.mark.parametrize("N,posmode,side,rmin", [(4096, 1, 120.0, 1.6), (4098, 2, 120.0, 1.6), (8192, 1, 170.0, 1.6), (8194, 1, 90.0, 1.8), (8702, 2, 100.0, 1.6)])
+@pytest.mark.parametrize("N,posmode,side,rmin", [(4096, 1, 120.0, 1.6), (4098, 2, 120.0, 1.6), (8192, 1, 170.0, 1.6), (8194, 1, 90.0, 1.8), (8702, 2, 100.0, 1.6),
+                                               (8704, 1, 170.0, 1.6), (8706, 1, 90.0, 1.8), (9214, 2, 100.0, 1.6)])
 def test_steric_contacts_against_fp64(N, posmode, side, rmin):
     """Contacts across chunks and blocks, dense enough that several lie in one
     group of steps; the FP64 form sums every pair."""
