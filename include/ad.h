@@ -104,9 +104,10 @@ typedef struct ad_params {
  * AD_FP64 with fused = 0 validates ipl, jchunk, wg and wj but its pair
  * kernel does not use them: a work-group of one or two producer waves and a
  * consumer wave per 2 or 4 target spheres, every source of the system in
- * ascending order. Nor do the steps of AD_FP32C with fused = 0 for one large
- * system (from 8704 spheres with hi/lo positions, 13312 with single floats,
- * 4096 with steric forces): their pair kernel forms every unordered pair once.
+ * ascending order (from 4096 systems of 64 spheres or fewer on average a thread
+ * per target, where the shape has one). Nor do the steps of AD_FP32C with fused = 0 for one large
+ * system (from 8704 spheres with hi/lo positions or steric forces, 13312 with
+ * single floats): their pair kernel forms every unordered pair once.
  * ad_mobility_apply uses the shape in every case. */
 typedef struct ad_launch {
     int32_t ipl;      /* target spheres per lane: 1, 2 or 4 (FP64 modes: 1 or 2; dense: 1) */

@@ -321,17 +321,28 @@ __host__ __device__ inline int fused_wide_lds_bytes(int n, int split) {
  * 2048 94, 77, 101, 85, 117; 4096 -, 306, 193, 214, 222; 5000 -, 430, 458,
  * 315, 374; 8192 -, 999, 970, 784, 689; 16384 -, 3612, 3536, 2860, 3021. RPY,
  * from {2,1,128}: 3072 174, 183, 180, 202; 6144 701, 880, 652, 597; 8192
- * 1195, 1537, 1120, 1303; 16384 4367, 5552, 4234, 4180. */
+ * 1195, 1537, 1120, 1303; 16384 4367, 5552, 4234, 4180. Ensembles of small
+ * systems, of which a chunk of 64 is all or most, take the last shape, with the
+ * most blocks resident: 512 systems of 32 spheres 42 ({4,2,64} 56), of 128 155
+ * (190), 128 of 512 414 (425); RPY 64 of 128 42 (52), but 10 of 686 130 (111). */
 struct F64WShape {
     int tw, np, cw; /* targets, producer waves, sources per chunk */
 };
-__host__ __device__ inline F64WShape f64w_shape(int Ntot, int rpy) {
+__host__ __device__ inline F64WShape f64w_shape(int Ntot, int rpy, int nsys) {
+    if (nsys > 1 && Ntot > 2560 && Ntot / nsys <= (rpy ? 256 : 768)) return {4, 1, 64};
     if (Ntot <= 1536) return {2, 2, 64};
     if (Ntot <= (rpy ? 3072 : 2560)) return {2, 1, 128};
     if (rpy) return Ntot > 6144 && Ntot <= 8192 ? F64WShape{4, 2, 64} : F64WShape{4, 1, 64};
     if (Ntot <= 4096) return {4, 1, 128};
     return Ntot > 5120 && Ntot <= 8192 ? F64WShape{4, 1, 64} : F64WShape{4, 2, 64};
 }
+/* Many small systems have more work-groups than are resident, each with the
+ * fixed cost of a block's waves and barriers: a thread per target (k_pairs_f64,
+ * the same bits) is faster from about 4096 systems. us per RK4 step, blocks and
+ * threads: 2048 dumbbells 23.5 and 30, 4096 39 and 33, 30000 190 and 108;
+ * systems of 16 spheres, 512 24 and 40, 4096 118 and 92; of 64 spheres, 1024
+ * 116 and 134, 4096 392 and 275. */
+inline bool f64_by_threads(int nsys, int Ntot) { return nsys >= 4096 && Ntot / nsys <= 64; }
 /* LDS of a work-group: two sets of np chunk buffers of rows x (cw + 2) */
 __host__ __device__ inline int f64w_lds_bytes(const F64WShape& f, int rpy) {
     return 2 * f.np * (rpy ? 6 : 3) * f.tw * (f.cw + 2) * 8;

@@ -3297,14 +3297,15 @@ hipError_t launch_state_out(const Dev& d, double* Xa, hipStream_t s) {
 /* Spheres per wave in the full steric sums (add_steric), 0 where a thread
  * takes a dumbbell: the thread's chain is 0.28 us per sphere of its system,
  * the wave's work 0.0006 us per dumbbell, so from about 1000 systems on the
- * threads are faster, whatever the systems' size (ad_forces, us, thread and
+ * threads are faster, whatever the systems' size, and for one or two dumbbells
+ * a system always (64 dumbbells, FP64 step, 36 us and 38; ad_forces, us, thread and
  * wave: 512 systems of 8 spheres 10 and 10, of 200 73 and 35; 8192 of 8 13 and
  * 16; 30000 of 4 10 and 26; a single one of 4096 spheres 1174 and 19). Eight
  * spheres share a wave's loads of a source where that leaves enough waves:
  * 4096 spheres 28 us (two: 19), 16384 119 (145), 65536 1.49 ms (2.28; by
  * threads 18.8). */
 static int steric_spheres(const Dev& d, const Coef& c) {
-    if (c.ks == 0.0 || d.nsys >= 1024) return 0;
+    if (c.ks == 0.0 || d.nsys >= 1024 || d.Ntot <= 4 * d.nsys) return 0;
     return d.nsys == 1 && d.Ntot >= 16384 ? 8 : 2;
 }
 static dim3 steric_grid(const Dev& d, int it) {
@@ -3385,9 +3386,8 @@ static hipError_t f64_ten(const Dev& d, const Epi& e, const Shape& sh, int mode,
     return sh.rpy ? go(k_pairs_f64<WG, IPL, 1>, WG, d, e, mode, s, tm) : go(k_pairs_f64<WG, IPL, 0>, WG, d, e, mode, s, tm);
 }
 
-template <int IPL>
+template <int IPL, int G>
 static hipError_t go_f64t(const Dev& d, const Epi& e, const Shape& sh, int mode, hipStream_t s, const Timing& tm) {
-    constexpr int G = 4;
     const int per_item = sh.wg / 64;
     const dim3 grid(d.nitems * per_item), block(64 * G);
     auto kern = sh.rpy ? k_pairs_f64t<G, IPL, 1> : k_pairs_f64t<G, IPL, 0>;
@@ -3423,7 +3423,7 @@ hipError_t launch_pairs(const Dev& d, const Epi& e, const Shape& sh, int mode, h
     }
     /* AD_FP64: the terms spread over waves (work list of target blocks) */
     if (e.prec == PREC_FP64 && d.f64_blocks && d.nfitems > 0) {
-        const F64WShape f = f64w_shape(d.Ntot, sh.rpy);
+        const F64WShape f = f64w_shape(d.Ntot, sh.rpy, d.nsys);
         if (f.tw == 4 && f.np == 2 && f.cw == 64) return go_f64w<4, 2, 64>(d, e, sh, mode, s, tm);
         if (f.tw == 4 && f.np == 1 && f.cw == 64) return go_f64w<4, 1, 64>(d, e, sh, mode, s, tm);
         if (f.tw == 4 && f.np == 1 && f.cw == 128 && !sh.rpy) return go_f64w<4, 1, 128>(d, e, sh, mode, s, tm);
@@ -3435,8 +3435,12 @@ hipError_t launch_pairs(const Dev& d, const Epi& e, const Shape& sh, int mode, h
      * work list was built for this shape, so anything else is refused */
     if (sh.wj != 1 || (sh.wg != 64 && sh.wg != 256)) return hipErrorInvalidValue;
     if (e.prec == PREC_FP64_TILED) {
-        if (sh.ipl == 1) return go_f64t<1>(d, e, sh, mode, s, tm);
-        if (sh.ipl == 2) return go_f64t<2>(d, e, sh, mode, s, tm);
+        /* one wave per 64 targets where a system's sources are one wave's
+         * (4096 systems of 16 spheres 69 us per RK4 step, with four 98; 30000
+         * dumbbells 108, 252) */
+        const bool small = d.nsys > 1 && d.Ntot / d.nsys <= 64;
+        if (sh.ipl == 1) return small ? go_f64t<1, 1>(d, e, sh, mode, s, tm) : go_f64t<1, 4>(d, e, sh, mode, s, tm);
+        if (sh.ipl == 2) return small ? go_f64t<2, 1>(d, e, sh, mode, s, tm) : go_f64t<2, 4>(d, e, sh, mode, s, tm);
         return hipErrorInvalidValue;
     }
     if (sh.wg == 64 && sh.ipl == 1) return f64_ten<64, 1>(d, e, sh, mode, s, tm);

@@ -76,7 +76,7 @@ StaticLayout static_layout(int prec, int rpy, int N, const ad::PairShape& sh, bo
     L.sys_P = take(4);
     L.sys_pbase = take(8);
     L.items = take((size_t)L.nitems * sizeof(Item));
-    L.tw = ad::f64w_shape(N, rpy).tw;
+    L.tw = ad::f64w_shape(N, rpy, 1).tw;
     L.nfitems = prec == ad::PREC_FP64 && fp64_blocks ? (N + L.tw - 1) / L.tw : 0;
     L.fitems = take((size_t)L.nfitems * sizeof(Item));
     L.pA = take(f32 ? n * 16 : 0);

@@ -252,6 +252,16 @@ static int validate_launch(ad_ctx* c, const ad_launch& L) {
 /* FP32C with steric forces: the pair kernel records steric candidates */
 static bool uses_lists(const ad_ctx* c) { return c->p.steric_k != 0.0 && c->p.precision == AD_FP32C; }
 
+/* AD_FP64 with two kernels per stage: by blocks of targets (k_pairs_f64w),
+ * unless there are many small systems and the launch shape is one that the
+ * thread-per-target kernel has */
+static bool f64_blocks(const ad_ctx* c) {
+    const ad_launch& L = c->launch;
+    if (c->p.precision != AD_FP64 || L.fused != 0) return false;
+    const bool threads = L.wj == 1 && (L.wg == 64 || L.wg == 256) && (L.ipl == 1 || L.ipl == 2);
+    return !(threads && ad::f64_by_threads(c->nsys, c->Ntot));
+}
+
 static ad::Shape shape_of(const ad_ctx* c) {
     ad::Shape sh;
     sh.wg = c->launch.wg;
@@ -388,8 +398,8 @@ static void build_items(ad_ctx* c) {
      * TW targets (one work-group each), longest system first (ad_kernels.hip,
      * k_pairs_f64w) */
     c->fitems.clear();
-    if (c->p.precision == AD_FP64 && L.fused == 0) {
-        const int tb = ad::f64w_shape(c->Ntot, c->coef.rpy).tw;
+    if (f64_blocks(c)) {
+        const int tb = ad::f64w_shape(c->Ntot, c->coef.rpy, c->nsys).tw;
         for (int b = 0; b < c->nsys; ++b) {
             const int Nb = 2 * c->S[b];
             for (int i = 0; i < Nb; i += tb) {
@@ -531,7 +541,7 @@ static void make_dev(ad_ctx* c) {
     d.H = c->nH ? reinterpret_cast<double*>(b + L.H) : nullptr;
     d.fitems = reinterpret_cast<const Item*>(b + L.fitems);
     d.nfitems = (int)c->fitems.size();
-    d.f64_blocks = c->p.precision == AD_FP64 && c->launch.fused == 0;
+    d.f64_blocks = f64_blocks(c);
     d.sym_items = reinterpret_cast<const Item*>(b + L.sitems);
     d.sym_base = reinterpret_cast<const long long*>(b + L.sbase);
     d.sym_P = reinterpret_cast<const int*>(b + L.sP);

@@ -120,3 +120,28 @@ def test_fp64_coincident_spheres_flagged_and_skipped(oracle, precision):
     assert s.check() == P.binding.AD_ENONFINITE
     o = oracle.mobility(Params(), X, F, allow_nonfinite=True)
     assert np.linalg.norm(u - o) <= 1e-13 * np.linalg.norm(o)
+
+
+@pytest.mark.parametrize("tensor", ["oseen", "rpy"])
+@pytest.mark.parametrize("precision", ["fp64", "fp64_tiled"])
+@pytest.mark.parametrize("W,S", [(1300, 1), (160, 9), (21, 127), (21, 129), (10, 300), (4095, 1), (4096, 1), (4100, 2)])
+def test_ensembles_of_small_systems(oracle, W, S, precision, tensor):
+    """The block shape of small systems, and a thread per target from 4096
+    systems on: two steps, some systems against the oracle's run."""
+    rng = np.random.default_rng(W)
+    ens = [make_single(S, 12.0 * S ** (1 / 3) + 20.0, 40 + b) for b in range(min(W, 7))]
+    X = np.concatenate([ens[b % len(ens)].X for b in range(W)])
+    phi = rng.uniform(0.0, 6.0, W * S)
+    s = P.Simulator(Params(), [S] * W, precision=precision, tensor=tensor)
+    s.set_state(X, phi)
+    s.step(2)
+    got = s.get_state()[0].cpu().numpy()
+    assert s.check() == 0
+    for b in {0, 1, W // 2, W - 1}:
+        x, p = slice(2 * S * b, 2 * S * (b + 1)), slice(S * b, S * (b + 1))
+        want = oracle.run(Params(), X[x], phi[p], 2, tensor=int(tensor == "rpy"))[0]
+        if precision == "fp64":
+            assert np.array_equal(got[x], want)
+        else:
+            # sums of at most 600 terms in another order, of a displacement
+            assert np.abs(got[x] - want).max() <= 1e-12 * np.abs(want - X[x]).max() + 1e-14 * np.abs(X[x]).max()
