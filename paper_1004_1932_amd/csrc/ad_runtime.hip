@@ -815,7 +815,7 @@ static int advance(ad_ctx* c, long long nsteps, int record_every, double* centre
         if (rc != AD_OK) return rc;
     }
     /* the resident kernel takes the step index as an argument: one launch less
-     * per call (a step of 27 dumbbells read back each time: 29.6 us with it) */
+     * per call (about 2 us of the 28 that a step of 27 dumbbells, read back each time, takes) */
     if (!c->slot_valid && !resident) HIPCHECK(c, ad::launch_set_step(c->dev, c->step, st));
     c->slot_valid = false; /* until this call completes */
     if (!c->pack_valid && !resident) {
