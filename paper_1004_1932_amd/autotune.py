@@ -65,10 +65,12 @@ def tuned_launch(S_per_sys, path: Path = TABLE):
 
 # the plain FP64 forms take the resident form (one work-group per system, every
 # stage of a run of steps in one launch; bitwise the same sums as the
-# two-kernel form) up to this many spheres per system: 16 spheres 4.4 us per
-# step against 34 for two kernels per stage, 64 lattices of 27 dumbbells 24
-# against 70. Past about 64 spheres its term chunks become long sequential
-# loops per thread and the two-kernel form wins.
+# form with a launch per stage) up to this many spheres per system: us per
+# AD_FP64 step, resident and a launch per stage replayed from graphs, 16 spheres
+# 3.9 and 13.2, 32 9.3 and 13.6, 512 lattices of 27 dumbbells 32 and 62. Its
+# term chunks become long sequential loops per thread as systems grow: of a
+# single system of 54 spheres it takes 23 us (13.6 replayed; launched one by
+# one, a stage's launch alone is about 5).
 RESIDENT_FP64_MAX = 64
 RESIDENT_FP64 = {"ipl": 1, "jchunk": 128, "wg": 64, "wj": 1, "posmode": 0, "fused": 4}
 

@@ -3,7 +3,8 @@
  * active spring dumbbell suspensions (Putz, Dunkel, Yeomans, Sec. II and
  * Sec. V).
  *
- * One RK4 stage is two launches:
+ * In the two-kernel form one RK4 stage is two launches (the fused stage
+ * kernels, the resident ones and k_pairs_f64w do both parts in one):
  *   k_pairs_*   the O(N^2) pair sum over a work list of (i-block, j-chunk)
  *               items; each item stages its j-tiles through LDS and every
  *               lane holds IPL consecutive target spheres in registers.
