@@ -143,12 +143,12 @@ __device__ __forceinline__ double sa_rates(const SaCoef& k, int S, int i, const 
             iD = 1.0 / D;
             sn = sin(ph);
         }
-        sn = self ? 0.0 : sn;
         const double ux = Dx * iD, uy = Dy * iD, uz = Dz * iD;
         const double s = __builtin_fma(uz, ni[2], __builtin_fma(uy, ni[1], ux * ni[0]));
         const double r = __builtin_fma(uz, nj[2], __builtin_fma(uy, nj[1], ux * nj[0]));
         const double q = __builtin_fma(ni[2], nj[2], __builtin_fma(ni[1], nj[1], ni[0] * nj[0]));
-        const double x = k.ell * iD, x2 = x * x, fj = sn * (x2 * x2);
+        const double x = k.ell * iD, x2 = x * x;
+        const double fj = self ? 0.0 : sn * (x2 * x2); /* x is ell there: its fourth power may overflow */
         const double sr = s * r, q2 = q + q;
         /* 2s + 4qr - 10 s r^2 */
         const double aN = __builtin_fma(r, __builtin_fma(-10.0, sr, q2 + q2), s + s);
