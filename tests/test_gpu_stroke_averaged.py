@@ -43,3 +43,52 @@ def test_own_term_of_large_lengths(oracle, S):
     _rates_match(oracle, p, R * 1e80, N, phi)
     one = P.StrokeAveraged(p, R[:1], N[:1], phi[:1]).rhs()
     assert all((v == 0.0).all() for v in one)
+
+
+@pytest.mark.parametrize("S", [1023, 1024, 1025, 1026, 1027, 1028, 2501])
+def test_rates_around_the_change_of_waves_per_dumbbell(oracle, S):
+    """Four waves a dumbbell up to 1024, one above: every remainder of the last
+    work-group's four dumbbells."""
+    _rates_match(oracle, Params(), *_config(S, S))
+
+
+@pytest.mark.parametrize("S", [1024, 1027])
+def test_run_around_the_change_of_waves_per_dumbbell(oracle, S):
+    p = Params()
+    R, N, phi = _config(S, S)
+    sa = P.StrokeAveraged(p, R, N, phi)
+    assert sa.run(5.0, 7) == 0
+    Ro, No = oracle.sa_run(p, R, N, phi, 5.0, 7)
+    Rg, Ng = sa.R.cpu().numpy(), sa.N.cpu().numpy()
+    # the displacement against positions up to 440: 7 steps' roundings of them
+    assert np.abs((Rg - R) - (Ro - R)).max() <= 8 * np.spacing(np.abs(R).max()) + 1e-12 * np.abs(Ro - R).max()
+    assert np.abs(Ng - No).max() <= 1e-13
+
+
+@pytest.mark.parametrize("S", [5, 1030])
+def test_coincident_centres_are_flagged_and_left_out(oracle, S):
+    R, N, phi = _config(S, S)
+    R[S - 1] = R[1]
+    assert P.StrokeAveraged(Params(), R, N, phi).run(1.0, 1) == P.binding.AD_ENONFINITE
+    keep = np.arange(S) != 1  # the others' rates do not depend on the flag
+    got = P.StrokeAveraged(Params(), R, N, phi).rhs()[0].cpu().numpy()
+    assert np.isfinite(got[keep]).all()
+
+
+@pytest.mark.parametrize("S", [40, 1030])
+@pytest.mark.parametrize("case", ["phases", "some phases", "close", "far", "one far"])
+def test_operands_the_short_forms_do_not_take(oracle, case, S):
+    """Phase differences from 2^19 on, D^2 outside 2^+-900, in every lane and
+    in some."""
+    p = Params()
+    R, N, phi = _config(S, S)
+    if case == "phases":
+        phi = phi + 2.0 ** 19 * 1.5 * np.arange(S)
+    elif case == "some phases":
+        phi[::7] += 3e6
+    elif case in ("close", "far"):
+        f = 1e-138 if case == "close" else 1e137
+        R, p = R * f, replace(p, a=f, ell=4 * f, lam=f)
+    else:
+        R[S // 2] = [1e140, 0.0, 0.0]
+    _rates_match(oracle, p, R, N, phi)
