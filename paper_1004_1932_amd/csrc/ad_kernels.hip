@@ -918,7 +918,8 @@ __global__ __launch_bounds__(WG) void k_pairs_f32c(Dev d, Epi e, int mode) {
                         }
                         ir[q][u] = __builtin_fmaf(rz[q][u], rz[q][u],
                                                   __builtin_fmaf(ry[q][u], ry[q][u], rx[q][u] * rx[q][u]));
-                        if (STERIC && ir[q][u] < d.list_r2 && ib + q < iend)
+                        /* (the padding past jend may be in reach where lengths are near its 1e15) */
+                        if (STERIC && ir[q][u] < d.list_r2 && ib + q < iend && t0 + jj + u < jend)
                             append(d.nbr_cnt, d.nbr_idx, &d.ctl->flag, ib + q, t0 + jj + u);
                     }
                 }

@@ -191,7 +191,7 @@ __global__ __launch_bounds__(64 * NW) void k_pairs_sym(Dev d, Epi e) {
                 for (int q = 0; q < IPL; ++q) {
                     float rx, ry, rz;
                     const float r2 = separation(q, A, B, rx, ry, rz);
-                    if (STERIC && r2 < d.list_r2 && j != ib + q && ib + q < N)
+                    if (STERIC && r2 < d.list_r2 && j != ib + q && ib + q < N && j < N)
                         append(d.nbr_cnt, d.nbr_idx, &d.ctl->flag, ib + q, j);
                     Pair<RPY> pr;
                     pr.set(rx, ry, rz, (j >> 1) == (ib >> 1) ? 0.f : rsq1(r2), crr);
@@ -255,8 +255,10 @@ __global__ __launch_bounds__(64 * NW) void k_pairs_sym(Dev d, Epi e) {
 #pragma unroll
                         for (int q = 0; q < IPL; ++q) {
                             float rx, ry, rz;
-                            if (separation(q, A, B, rx, ry, rz) < d.list_r2) {
-                                const int j = c * 64 + row * 16 + (at & 15);
+                            const int j = c * 64 + row * 16 + (at & 15);
+                            /* lanes and entries past the end stand far off, but not
+                             * out of reach where lengths are near 1e15 */
+                            if (separation(q, A, B, rx, ry, rz) < d.list_r2 && ib + q < N && j < N) {
                                 append(d.nbr_cnt, d.nbr_idx, &d.ctl->flag, ib + q, j);
                                 append(d.nbr_cnt, d.nbr_idx, &d.ctl->flag, j, ib + q);
                             }
