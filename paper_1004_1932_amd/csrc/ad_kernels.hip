@@ -756,11 +756,12 @@ struct Target {
 };
 
 /* Four terms of a fused stage, from the LDS entries x0, x0 + dx, x0 + 2 dx and
- * x0 + 3 dx: none masked. Their v_rsq_f32 together, see rsq4. */
-template <int SPLIT, int RPY, int PRIO>
+ * x0 + 3 dx; with MASK but for those of dumbbell `skip`. Their v_rsq_f32
+ * together, see rsq4. */
+template <int SPLIT, int RPY, int PRIO, int MASK = 0>
 __device__ __forceinline__ void four_terms(const Target& t, const float4* sA, const float4* sB, const float* sC,
                                            const float2* sF, int x0, int dx, float crr, float& px, float& py,
-                                           float& pz) {
+                                           float& pz, int skip = 0) {
     float rx[4], ry[4], rz[4], fx[4], fy[4], fz[4], ir[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -785,6 +786,10 @@ __device__ __forceinline__ void four_terms(const Target& t, const float4* sA, co
         ir[u] = __builtin_fmaf(rz[u], rz[u], __builtin_fmaf(ry[u], ry[u], rx[u] * rx[u]));
     }
     rsq4<PRIO>(ir);
+    if (MASK) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) ir[u] = ((x0 + u * dx) >> 1) == skip ? 0.f : ir[u];
+    }
 #pragma unroll
     for (int u = 0; u < 4; ++u) pair_term<RPY>(ir[u], rx[u], ry[u], rz[u], fx[u], fy[u], fz[u], crr, px, py, pz);
 }
@@ -1305,7 +1310,10 @@ __global__ __launch_bounds__(64 * NW) void k_stage_fused(Dev d, Epi e) {
  * the sources of its quarter [w Q, (w + 1) Q) of the padded source list
  * (Q = np / 4), each read as an LDS broadcast, in FP32 with a TwoSum into
  * (hi, lo) every FW_M sources. Only the sources that are the work-group's own
- * spheres need the self/partner test. The quarters' sums of a target are
+ * spheres need the self/partner test; they go four at a time too (one at a
+ * time, each waiting for its own LDS reads, a work-group waited for the wave
+ * that holds them: 128 systems of 16 to 200 dumbbells 51.0 us per RK4 step, 40.8
+ * this way; 512 of 16 to 400 229 and 220). The quarters' sums of a target are
  * combined through LDS as (q0 + q1) + (q2 + q3), and the closing update is
  * the one of k_stage_fused. Per work-group, staging and the closing update
  * cost what they cost for 16 targets, over four times the pair work. */
@@ -1410,9 +1418,11 @@ __global__ __launch_bounds__(256) void k_stage_wide(Dev d, Epi e) {
         pair_term<RPY>(ir, rx, ry, rz, Aj.w, Fy, Fz, crr, px, py, pz);
     };
     const Target me{hx, hy, hz, lx, ly, lz};
-    auto quad = [&](int x0, int dx, float& px, float& py, float& pz) {
-        four_terms<SPLIT, RPY, 1>(me, sA, sB, sC, sF, x0, dx, crr, px, py, pz);
+    auto quad = [&](int x0, auto mask_c, float& px, float& py, float& pz) {
+        four_terms<SPLIT, RPY, 1, decltype(mask_c)::value>(me, sA, sB, sC, sF, x0, 1, crr, px, py, pz, di);
     };
+    constexpr std::integral_constant<int, 0> plain{};
+    constexpr std::integral_constant<int, 1> masked{};
     /* this wave's quarter of the sources, and the part of it that holds the
      * work-group's own spheres (local [i0 - off, i0 - off + ni)) */
     const int j0 = w * Q, j1 = j0 + Q;
@@ -1421,12 +1431,14 @@ __global__ __launch_bounds__(256) void k_stage_wide(Dev d, Epi e) {
         const int c1 = min(j1, c0 + FW_M);
         float px = 0.f, py = 0.f, pz = 0.f;
         if (c0 < jm1 && c1 > jm0) {
-            for (int j = c0; j < c1; ++j) term(j, true, px, py, pz);
+            int j = c0;
+            for (; j + 4 <= c1; j += 4) quad(j, masked, px, py, pz);
+            for (; j < c1; ++j) term(j, true, px, py, pz);
         } else if (c1 - c0 == FW_M) {
-            for (int j = c0; j < c0 + FW_M; j += 4) quad(j, 1, px, py, pz);
+            for (int j = c0; j < c0 + FW_M; j += 4) quad(j, plain, px, py, pz);
         } else {
             int j = c0;
-            for (; j + 4 <= c1; j += 4) quad(j, 1, px, py, pz);
+            for (; j + 4 <= c1; j += 4) quad(j, plain, px, py, pz);
             for (; j < c1; ++j) term(j, false, px, py, pz);
         }
         two_sum_acc(ax, bx, px);
