@@ -1072,9 +1072,13 @@ __device__ __forceinline__ void wave_add_hilo(float v[6]) {
  * further barrier: a stage needs no partial sums in HBM and no second
  * launch. Only the one term of the
  * JS-source block that holds the work-group's own dumbbells needs the
- * self/partner mask. A single system uses NW = 16 and target blocks in
- * order; an ensemble NW = 4 and a work list of (system, target block),
- * longest system first. */
+ * self/partner mask, so only its group of four has it. A single system uses
+ * NW = 16 and target blocks in order; an ensemble NW = 4 and a work list of
+ * (system, target block), longest system first. The groups' loops are not
+ * unrolled further: two groups in flight took 111 registers, four waves per
+ * SIMD, and ensembles, whose many small work-groups hide each other's
+ * latencies, want the six that 80 registers allow (500 systems of 125 dumbbells
+ * 126 us per RK4 step unrolled, 101 not; 64 of 343 82 and 75; one of 1000 35.2 and 35.1). */
 constexpr int FS_I = 16;
 
 /* One source entry of the fused stage: sphere t0 + t of the pack, or
@@ -1221,27 +1225,34 @@ __global__ __launch_bounds__(64 * NW) void k_stage_fused(Dev d, Epi e) {
         pair_term<RPY>(ir, rx, ry, rz, Aj.w, Fy, Fz, crr, px, py, pz);
     };
     const Target me{hx, hy, hz, lx, ly, lz};
-    auto quad = [&](int x0, int dx, float& px, float& py, float& pz) {
-        four_terms<SPLIT, RPY, 1>(me, sA, sB, sC, sF, x0, dx, crr, px, py, pz);
+    auto quad = [&](int x0, auto mask_c, float& px, float& py, float& pz) {
+        four_terms<SPLIT, RPY, 1, decltype(mask_c)::value>(me, sA, sB, sC, sF, x0, JS, crr, px, py, pz, di);
     };
+    constexpr std::integral_constant<int, 0> plain{};
+    constexpr std::integral_constant<int, 1> masked{};
     const int M = np / JS;
     const int ms = (i0 - off) / JS; /* the source block holding this group's dumbbells */
     for (int m0 = 0; m0 < M; m0 += FS_M) {
         const int m1 = min(M, m0 + FS_M);
         float px = 0.f, py = 0.f, pz = 0.f;
         if (ms >= m0 && ms < m1) {
+            const int mq = m0 + ((ms - m0) & ~3); /* the group of four that holds ms */
             int m = m0;
-            for (; m + 4 <= ms; m += 4) quad(js + JS * m, JS, px, py, pz);
-            for (; m < ms; ++m) term(js + JS * m, false, px, py, pz);
-            term(js + JS * ms, true, px, py, pz);
-            for (m = ms + 1; m + 4 <= m1; m += 4) quad(js + JS * m, JS, px, py, pz);
-            for (; m < m1; ++m) term(js + JS * m, false, px, py, pz);
+#pragma unroll 1
+            for (; m < mq; m += 4) quad(js + JS * m, plain, px, py, pz);
+            if (m + 4 <= m1) {
+                quad(js + JS * m, masked, px, py, pz);
+                m += 4;
+            }
+#pragma unroll 1
+            for (; m + 4 <= m1; m += 4) quad(js + JS * m, plain, px, py, pz);
+            for (; m < m1; ++m) term(js + JS * m, true, px, py, pz);
         } else if (m1 - m0 == FS_M) {
-#pragma unroll 2
-            for (int m = m0; m < m0 + FS_M; m += 4) quad(js + JS * m, JS, px, py, pz);
+#pragma unroll 1
+            for (int m = m0; m < m0 + FS_M; m += 4) quad(js + JS * m, plain, px, py, pz);
         } else {
             int m = m0;
-            for (; m + 4 <= m1; m += 4) quad(js + JS * m, JS, px, py, pz);
+            for (; m + 4 <= m1; m += 4) quad(js + JS * m, plain, px, py, pz);
             for (; m < m1; ++m) term(js + JS * m, false, px, py, pz);
         }
         two_sum_acc(ax, bx, px);
