@@ -185,6 +185,14 @@ __device__ __forceinline__ void rsq4(float x[4]) {
         asm("s_nop 0\n\tv_rsq_f32 %0, %0\n\tv_rsq_f32 %1, %1\n\tv_rsq_f32 %2, %2\n\tv_rsq_f32 %3, %3\n\ts_nop 0"
             : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
 }
+/* for two */
+template <int PRIO>
+__device__ __forceinline__ void rsq2(float x[2]) {
+    if (PRIO)
+        asm("s_setprio 3\n\tv_rsq_f32 %0, %0\n\tv_rsq_f32 %1, %1\n\ts_setprio 0" : "+v"(x[0]), "+v"(x[1]));
+    else
+        asm("s_nop 0\n\tv_rsq_f32 %0, %0\n\tv_rsq_f32 %1, %1\n\ts_nop 0" : "+v"(x[0]), "+v"(x[1]));
+}
 /* and for one */
 __device__ __forceinline__ float rsq1(float x) {
     asm("s_setprio 3\n\tv_rsq_f32 %0, %0\n\ts_setprio 0" : "+v"(x));

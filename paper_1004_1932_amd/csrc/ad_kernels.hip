@@ -755,16 +755,16 @@ struct Target {
     float hx, hy, hz, lx, ly, lz;
 };
 
-/* Four terms of a fused stage, from the LDS entries x0, x0 + dx, x0 + 2 dx and
- * x0 + 3 dx; with MASK but for those of dumbbell `skip`. Their v_rsq_f32
- * together, see rsq4. */
-template <int SPLIT, int RPY, int PRIO, int MASK = 0>
-__device__ __forceinline__ void four_terms(const Target& t, const float4* sA, const float4* sB, const float* sC,
+/* G = 4 (or 2) terms of a fused stage, from the LDS entries x0, x0 + dx, ...;
+ * with MASK but for those of dumbbell `skip`. Their v_rsq_f32 together, see
+ * rsq4. */
+template <int SPLIT, int RPY, int PRIO, int MASK = 0, int G = 4>
+__device__ __forceinline__ void group_terms(const Target& t, const float4* sA, const float4* sB, const float* sC,
                                            const float2* sF, int x0, int dx, float crr, float& px, float& py,
                                            float& pz, int skip = 0) {
-    float rx[4], ry[4], rz[4], fx[4], fy[4], fz[4], ir[4];
+    float rx[G], ry[G], rz[G], fx[G], fy[G], fz[G], ir[G];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < G; ++u) {
         const int x = x0 + u * dx;
         const float4 A = sA[x];
         fx[u] = A.w;
@@ -785,13 +785,16 @@ __device__ __forceinline__ void four_terms(const Target& t, const float4* sA, co
         }
         ir[u] = __builtin_fmaf(rz[u], rz[u], __builtin_fmaf(ry[u], ry[u], rx[u] * rx[u]));
     }
-    rsq4<PRIO>(ir);
+    if (G == 4)
+        rsq4<PRIO>(ir);
+    else
+        rsq2<PRIO>(ir);
     if (MASK) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) ir[u] = ((x0 + u * dx) >> 1) == skip ? 0.f : ir[u];
+        for (int u = 0; u < G; ++u) ir[u] = ((x0 + u * dx) >> 1) == skip ? 0.f : ir[u];
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) pair_term<RPY>(ir[u], rx[u], ry[u], rz[u], fx[u], fy[u], fz[u], crr, px, py, pz);
+    for (int u = 0; u < G; ++u) pair_term<RPY>(ir[u], rx[u], ry[u], rz[u], fx[u], fy[u], fz[u], crr, px, py, pz);
 }
 
 /* One thread's entry of a source tile: sphere t0 + t of the pack, or
@@ -1226,7 +1229,7 @@ __global__ __launch_bounds__(64 * NW) void k_stage_fused(Dev d, Epi e) {
     };
     const Target me{hx, hy, hz, lx, ly, lz};
     auto quad = [&](int x0, auto mask_c, float& px, float& py, float& pz) {
-        four_terms<SPLIT, RPY, 1, decltype(mask_c)::value>(me, sA, sB, sC, sF, x0, JS, crr, px, py, pz, di);
+        group_terms<SPLIT, RPY, 1, decltype(mask_c)::value>(me, sA, sB, sC, sF, x0, JS, crr, px, py, pz, di);
     };
     constexpr std::integral_constant<int, 0> plain{};
     constexpr std::integral_constant<int, 1> masked{};
@@ -1430,7 +1433,7 @@ __global__ __launch_bounds__(256) void k_stage_wide(Dev d, Epi e) {
     };
     const Target me{hx, hy, hz, lx, ly, lz};
     auto quad = [&](int x0, auto mask_c, float& px, float& py, float& pz) {
-        four_terms<SPLIT, RPY, 1, decltype(mask_c)::value>(me, sA, sB, sC, sF, x0, 1, crr, px, py, pz, di);
+        group_terms<SPLIT, RPY, 1, decltype(mask_c)::value>(me, sA, sB, sC, sF, x0, 1, crr, px, py, pz, di);
     };
     constexpr std::integral_constant<int, 0> plain{};
     constexpr std::integral_constant<int, 1> masked{};
@@ -1658,8 +1661,13 @@ __device__ __forceinline__ void stage_stream(const Dev& d, const Epi& e) {
         pair_term<RPY>(ir, rx, ry, rz, Aj.w, Fy, Fz, crr, px, py, pz);
     };
     const Target me{hx, hy, hz, lx, ly, lz};
-    auto quad = [&](int x0, int dx, float& px, float& py, float& pz) {
-        four_terms<SPLIT, RPY, !BAL>(me, sA, sB, sC, sF, x0, dx, crr, px, py, pz);
+    /* terms per group: two with hi/lo positions and 8 targets, where groups of
+     * four took 128 to 131 registers and with RPY or noise left a compute unit
+     * one work-group (3072 spheres, RPY, us per RK4 step: 63.5, 54.8 this way; a
+     * cap at 128 spills, 56.8, and 27.2 against 28.4 at 1400) */
+    constexpr int NT = SPLIT && TI == 8 ? 2 : 4;
+    auto group = [&](int x0, float& px, float& py, float& pz) {
+        group_terms<SPLIT, RPY, !BAL, 0, NT>(me, sA, sB, sC, sF, x0, 1, crr, px, py, pz);
     };
     float px = 0.f, py = 0.f, pz = 0.f;
     auto chunk = [&](int k, auto R) {
@@ -1682,7 +1690,7 @@ __device__ __forceinline__ void stage_stream(const Dev& d, const Epi& e) {
                 for (int v = 0; v < TI; ++v) term(x0 + v, j0 + v, false, px, py, pz);
             } else {
 #pragma unroll
-                for (int v = 0; v < TI; v += 4) quad(x0 + v, 1, px, py, pz);
+                for (int v = 0; v < TI; v += NT) group(x0 + v, px, py, pz);
             }
         }
         if ((k + 1) % FOLD == 0 || k + 1 == K) {

@@ -58,3 +58,11 @@ def test_fused_stage_of_ensembles_holds_six_waves(kernels):
     """Its many work-groups of four waves hide each other's latencies."""
     for k, v in _of(kernels, "k_stage_fused", None, None, 4).items():
         assert _waves(v) >= 6 and v["vgpr_spill_count"] == 0, (k, v)
+
+
+@pytest.mark.parametrize("targets", [4, 8])
+def test_streamed_stage_of_eight_waves_shares_a_compute_unit(kernels, targets):
+    """Two work-groups of eight waves on a compute unit's four SIMDs, which from
+    2048 to 4095 spheres it is chosen for."""
+    for k, v in _of(kernels, "k_stage_stream", None, None, targets, 8, None).items():
+        assert _waves(v) >= 4 and v["vgpr_spill_count"] == 0, (k, v)
