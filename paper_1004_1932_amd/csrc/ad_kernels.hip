@@ -903,45 +903,62 @@ __global__ __launch_bounds__(WG) void k_pairs_f32c(Dev d, Epi e, int mode) {
         const int jw = WJ == 1 ? n : (n + 4 * WJ - 1) / (4 * WJ) * 4;
         const int jb = wj * jw;
         const int nw = max(0, min(jw, n - jb));
-        if (!diag) {
-            const int n4 = (nw + 3) & ~3;
+        /* Groups of four terms, IPL targets by SU sources (with four sources for
+         * every target the shapes of 4 targets per lane took 165 registers in
+         * place of 103 to 127). Where the tile holds some of the targets
+         * (MASK), what is left over goes source by source, and with steric
+         * forces everything, whose registers would cost more waves than the
+         * groups gain. Products, us, before and so: 128 spheres 19.9 and 18.6,
+         * 8000 with RPY 51.3 and 48.6; 2 targets per lane, four waves, 6000
+         * spheres 96.7 and 68.8; 4 targets, one wave, 12000 with RPY 175 and
+         * 128. */
+        auto sum = [&](auto mask_c) {
+            constexpr bool MASK = decltype(mask_c)::value;
+            constexpr int SU = 4 / IPL;
+            const int n4 = !MASK ? (nw + 3) & ~3 : STERIC ? 0 : nw & ~3;
             for (int jj = jb; jj < jb + n4; jj += 4) {
-                float4 Aj[4], Bj[4];
-                float Fz[4], rx[IPL][4], ry[IPL][4], rz[IPL][4], ir[IPL][4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    Aj[u] = sA[jj + u];
-                    Bj[u] = sB[jj + u];
-                    Fz[u] = sC[jj + u];
+                for (int g = 0; g < 4; g += SU) {
+                    const int u0 = jj + g;
+                    float4 Aj[SU], Bj[SU];
+                    float Fz[SU], rx[4], ry[4], rz[4], ir[4];
 #pragma unroll
-                    for (int q = 0; q < IPL; ++q) {
-                        if (SPLIT) {
-                            rx[q][u] = (hx[q] - Aj[u].x) + (lx[q] - Bj[u].x);
-                            ry[q][u] = (hy[q] - Aj[u].y) + (ly[q] - Bj[u].y);
-                            rz[q][u] = (hz[q] - Aj[u].z) + (lz[q] - Bj[u].z);
-                        } else {
-                            rx[q][u] = hx[q] - Aj[u].x;
-                            ry[q][u] = hy[q] - Aj[u].y;
-                            rz[q][u] = hz[q] - Aj[u].z;
+                    for (int u = 0; u < SU; ++u) {
+                        Aj[u] = sA[u0 + u];
+                        Bj[u] = sB[u0 + u];
+                        Fz[u] = sC[u0 + u];
+#pragma unroll
+                        for (int q = 0; q < IPL; ++q) {
+                            const int p = u * IPL + q;
+                            if (SPLIT) {
+                                rx[p] = (hx[q] - Aj[u].x) + (lx[q] - Bj[u].x);
+                                ry[p] = (hy[q] - Aj[u].y) + (ly[q] - Bj[u].y);
+                                rz[p] = (hz[q] - Aj[u].z) + (lz[q] - Bj[u].z);
+                            } else {
+                                rx[p] = hx[q] - Aj[u].x;
+                                ry[p] = hy[q] - Aj[u].y;
+                                rz[p] = hz[q] - Aj[u].z;
+                            }
+                            ir[p] = __builtin_fmaf(rz[p], rz[p], __builtin_fmaf(ry[p], ry[p], rx[p] * rx[p]));
+                            /* (the padding past jend may be in reach where lengths are near its 1e15) */
+                            if (STERIC && ir[p] < d.list_r2 && ib + q < iend && t0 + u0 + u < jend)
+                                append(d.nbr_cnt, d.nbr_idx, &d.ctl->flag, ib + q, t0 + u0 + u);
                         }
-                        ir[q][u] = __builtin_fmaf(rz[q][u], rz[q][u],
-                                                  __builtin_fmaf(ry[q][u], ry[q][u], rx[q][u] * rx[q][u]));
-                        /* (the padding past jend may be in reach where lengths are near its 1e15) */
-                        if (STERIC && ir[q][u] < d.list_r2 && ib + q < iend && t0 + jj + u < jend)
-                            append(d.nbr_cnt, d.nbr_idx, &d.ctl->flag, ib + q, t0 + jj + u);
                     }
+                    rsq4<1>(ir);
+#pragma unroll
+                    for (int u = 0; u < SU; ++u)
+#pragma unroll
+                        for (int q = 0; q < IPL; ++q) {
+                            const int p = u * IPL + q;
+                            if (MASK) ir[p] = (t0 + u0 + u) >> 1 == dq[q] ? 0.f : ir[p];
+                            pair_term<RPY>(ir[p], rx[p], ry[p], rz[p], Aj[u].w, Bj[u].w, Fz[u], crr, px[q], py[q],
+                                           pz[q]);
+                        }
                 }
-#pragma unroll
-                for (int q = 0; q < IPL; ++q) rsq4<1>(ir[q]);
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int q = 0; q < IPL; ++q)
-                        pair_term<RPY>(ir[q][u], rx[q][u], ry[q][u], rz[q][u], Aj[u].w, Bj[u].w, Fz[u], crr, px[q],
-                                       py[q], pz[q]);
             }
-        } else {
-            for (int jj = jb; jj < jb + nw; ++jj) {
+            if (!MASK) return;
+            for (int jj = jb + n4; jj < jb + nw; ++jj) {
                 const float4 Aj = sA[jj];
                 const float4 Bj = sB[jj];
                 const float Fz = sC[jj];
@@ -965,7 +982,11 @@ __global__ __launch_bounds__(WG) void k_pairs_f32c(Dev d, Epi e, int mode) {
                     pair_term<RPY>(ir, rx, ry, rz, Aj.w, Bj.w, Fz, crr, px[q], py[q], pz[q]);
                 }
             }
-        }
+        };
+        if (diag)
+            sum(std::integral_constant<bool, true>{});
+        else
+            sum(std::integral_constant<bool, false>{});
         /* TwoSum of the tile partial into (hi, lo) */
 #pragma unroll
         for (int q = 0; q < IPL; ++q) {

@@ -66,3 +66,8 @@ def test_streamed_stage_of_eight_waves_shares_a_compute_unit(kernels, targets):
     2048 to 4095 spheres it is chosen for."""
     for k, v in _of(kernels, "k_stage_stream", None, None, targets, 8, None).items():
         assert _waves(v) >= 4 and v["vgpr_spill_count"] == 0, (k, v)
+
+
+def test_pair_kernel_of_four_targets_per_lane_holds_four_waves(kernels):
+    for k, v in _of(kernels, "k_pairs_f32c", None, 4, None, None, 0, None).items():
+        assert _waves(v) >= 4 and v["vgpr_spill_count"] == 0, (k, v)
