@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "ad_internal.h"
@@ -2885,9 +2886,11 @@ __device__ __forceinline__ void combine_level_shfl(float v[6], int sh) {
  * and after: 2 spheres 4.04 and 3.88 us, 6 4.62 and 3.76, 14
  * 4.95 and 4.15, 16 4.35 and 3.80 (RPY 5.10 and 4.48); Heun with noise, 16
  * spheres: 3.92 and 2.44 us (the noise, the same in both stages, is formed in
- * the first). */
-template <int RPY, int INTEG>
-__global__ __launch_bounds__(RES_T) void k_resident(Dev d, Epi e, long long step0, int nsteps, double st0,
+ * the first).
+ * ONE = 0 is the kernel without that form, for more systems than are resident
+ * at once with it: 84 registers in place of 103, see resident_forms. */
+template <int RPY, int INTEG, int ONE>
+__global__ __launch_bounds__(RES_T, !ONE && RPY && INTEG == 2 ? 4 : 1) void k_resident(Dev d, Epi e, long long step0, int nsteps, double st0,
                                                     double ct0) {
     /* INTEG: 0 RK4, 1 Heun, 2 Heun with noise; the stages are unrolled, so
      * every stage's update and table entries are fixed at compile time */
@@ -2921,7 +2924,7 @@ __global__ __launch_bounds__(RES_T) void k_resident(Dev d, Epi e, long long step
     }
     /* one: at most one pair per thread, (pi, pj), which forms sphere pj's
      * spring force itself; else thread tid < n forms sphere tid's */
-    const bool one = n * n <= T;
+    const bool one = ONE && n * n <= T;
     const int pi = one ? tid / n : 0, pj = one ? tid - pi * n : tid;
     const bool springs = tid < (one ? n * n : n);
     double2 tp = make_double2(0.0, 0.0);
@@ -3016,11 +3019,11 @@ __global__ __launch_bounds__(RES_T) void k_resident(Dev d, Epi e, long long step
     if (!one) forces(fst, fct);
 
     auto stage_pass = [&](auto one_c, auto stage_c, long long step) {
-        constexpr bool ONE = decltype(one_c)::value;
+        constexpr bool one = decltype(one_c)::value;
         constexpr int stage = decltype(stage_c)::value;
         for (int j0 = 0; j0 < n; j0 += cc) {
             const int nc = min(cc, n - j0);
-            if constexpr (ONE) {
+            if constexpr (one) {
                 if (springs) pair_of_one(fst, fct);
             } else {
                 for (int p = tid; p < n * nc; p += T) {
@@ -3064,7 +3067,7 @@ __global__ __launch_bounds__(RES_T) void k_resident(Dev d, Epi e, long long step
                         if (RPY) bcc = bcc + w[u];
                     }
                 }
-                if constexpr (ONE) { /* the rest together too, +0.0 past the end */
+                if constexpr (one) { /* the rest together too, +0.0 past the end */
                     double v[8], w[8];
                     if (jb < nc) {
 #pragma unroll
@@ -3088,7 +3091,7 @@ __global__ __launch_bounds__(RES_T) void k_resident(Dev d, Epi e, long long step
                 Acc[q] = acc;
                 if (RPY) Bcc[q] = bcc;
             }
-            if (!ONE && j0 + cc < n) lds_barrier(); /* before the next chunk's terms */
+            if (!one && j0 + cc < n) lds_barrier(); /* before the next chunk's terms */
         }
         /* closing: each thread the (component, sphere) rows that it summed */
         for (int q = tid, w = 0; q < 3 * n; q += T, ++w) {
@@ -3113,7 +3116,7 @@ __global__ __launch_bounds__(RES_T) void k_resident(Dev d, Epi e, long long step
         lds_barrier();
         fst = tb[2 * stage];
         fct = tb[2 * stage + 1];
-        if (!ONE) forces(fst, fct);
+        if (!one) forces(fst, fct);
     };
     auto run = [&](auto one_c) {
         for (int sn = 0; sn < nsteps; ++sn) {
@@ -3130,10 +3133,10 @@ __global__ __launch_bounds__(RES_T) void k_resident(Dev d, Epi e, long long step
             for (int q = 0; q < 8; ++q) tb[q] = nb[q];
         }
     };
-    if (one)
-        run(std::integral_constant<bool, true>{});
-    else
-        run(std::integral_constant<bool, false>{});
+    if constexpr (ONE) {
+        if (one) run(std::integral_constant<bool, true>{});
+    }
+    if (!one) run(std::integral_constant<bool, false>{});
     for (int q = tid; q < 3 * n; q += T) {
         const int a = q / n, i = q - a * n;
         d.X[a * N + ioff + i] = X[q];
@@ -3593,6 +3596,33 @@ static ResidentKernel resident_c_threads(int hilo, int rpy, int integ) {
     return rpy ? resident_c_integ<0, 1, T>(integ) : resident_c_integ<0, 0, T>(integ);
 }
 
+template <int ONE>
+static ResidentKernel resident_form(int rpy, int integ) {
+    if (rpy) return integ == 0 ? k_resident<1, 0, ONE> : integ == 1 ? k_resident<1, 1, ONE> : k_resident<1, 2, ONE>;
+    return integ == 0 ? k_resident<0, 0, ONE> : integ == 1 ? k_resident<0, 1, ONE> : k_resident<0, 2, ONE>;
+}
+/* The FP64 resident kernel with the form of up to 16 spheres (one) or without. */
+static ResidentKernel resident_kernel(int one, int rpy, int integ) {
+    return one ? resident_form<1>(rpy, integ) : resident_form<0>(rpy, integ);
+}
+/* Which of the two. By their registers a compute unit holds with[] and
+ * without[] work-groups of them (or what LDS allows, if fewer). While every
+ * system is resident at once with the form, it is the faster one; beyond that
+ * it costs another round of work-groups where the other kernel needs none. Up
+ * to 8 spheres, whose pairs are one wave, it also pays for as many rounds as
+ * the other takes (up to 4 spheres for two). us per RK4 step, Oseen, with and
+ * without: 1024 systems of 10 spheres 5.67, 5.82, 1025 8.77, 6.63, 1536 10.5,
+ * 9.9, 4096 22.4, 20.3; of 6, 4096 18.9, 20.6; of 4, 1024 4.55, 5.22, 1280 8.70,
+ * 6.23, 1400 8.64, 10.5, 4096 19.4, 19.9; of 2, 4096 19.5, 18.7. */
+static bool resident_one(int rpy, int integ, int nsys, int maxNb, size_t lds) {
+    static const int with[2][3] = {{4, 5, 3}, {4, 4, 3}}, without[2][3] = {{5, 7, 4}, {4, 5, 4}};
+    const int by_lds = lds ? (int)(FUSED_LDS_MAX / lds) : 8;
+    const int w = 256 * std::min(with[rpy][integ], by_lds), o = 256 * std::min(without[rpy][integ], by_lds);
+    if (o <= w || nsys <= w) return true;
+    if (maxNb <= 4 && nsys > 2 * w) return false;
+    return maxNb <= 8 && (nsys + w - 1) / w <= (nsys + o - 1) / o;
+}
+
 /* the FP32C resident kernel for hi/lo positions or not, RPY or not, T
  * threads (64, 128, 256 or 512) and integrator integ (0 RK4, 1 Heun, 2 Heun
  * with noise) */
@@ -3643,12 +3673,11 @@ hipError_t prepare_fused() {
             return err;
         }
     }
-    const void* resident[54] = {
-        reinterpret_cast<const void*>(&k_resident<0, 0>), reinterpret_cast<const void*>(&k_resident<1, 0>),
-        reinterpret_cast<const void*>(&k_resident<0, 1>), reinterpret_cast<const void*>(&k_resident<1, 1>),
-        reinterpret_cast<const void*>(&k_resident<0, 2>), reinterpret_cast<const void*>(&k_resident<1, 2>)};
+    const void* resident[60];
+    for (int q = 0; q < 12; ++q)
+        resident[q] = reinterpret_cast<const void*>(resident_kernel(q & 1, (q >> 1) & 1, q >> 2));
     for (int q = 0; q < 48; ++q)
-        resident[6 + q] = reinterpret_cast<const void*>(
+        resident[12 + q] = reinterpret_cast<const void*>(
             resident_c_kernel(q & 1, (q >> 1) & 1, 64 << ((q >> 2) & 3), q >> 4));
     for (const void* k : resident) {
         hipError_t err = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, RES_LDS_MAX);
@@ -3672,9 +3701,7 @@ hipError_t launch_resident(const Dev& d, const Epi& e, int hilo, int maxNb, long
     ResidentKernel kern;
     const int integ = e.integ == 0 ? 0 : (e.c.noise ? 2 : 1);
     if (p64)
-        kern = integ == 0 ? (rpy ? k_resident<1, 0> : k_resident<0, 0>)
-               : integ == 1 ? (rpy ? k_resident<1, 1> : k_resident<0, 1>)
-                            : (rpy ? k_resident<1, 2> : k_resident<0, 2>);
+        kern = resident_kernel(resident_one(rpy, integ, d.nfitems, maxNb, lds), rpy, integ);
     else
         kern = resident_c_kernel(hilo, rpy, T, integ);
     if (ev_start)

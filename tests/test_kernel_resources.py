@@ -71,3 +71,16 @@ def test_streamed_stage_of_eight_waves_shares_a_compute_unit(kernels, targets):
 def test_pair_kernel_of_four_targets_per_lane_holds_four_waves(kernels):
     for k, v in _of(kernels, "k_pairs_f32c", None, 4, None, None, 0, None).items():
         assert _waves(v) >= 4 and v["vgpr_spill_count"] == 0, (k, v)
+
+
+def test_resident_kernels_hold_the_work_groups_their_rule_counts_on(kernels):
+    """The table in resident_one: work-groups per compute unit (one wave per
+    SIMD each) with and without the form of up to 16 spheres."""
+    src = (build.CSRC / "ad_kernels.hip").read_text()
+    rows = re.search(r"with\[2\]\[3\] = \{\{(.*?)\}, \{(.*?)\}\}, without\[2\]\[3\] = \{\{(.*?)\}, \{(.*?)\}\};", src)
+    table = [[int(x) for x in r.split(",")] for r in rows.groups()]
+    for one in (1, 0):
+        for rpy in (0, 1):
+            for integ in range(3):
+                (v,) = _of(kernels, "k_resident", rpy, integ, one).values()
+                assert _waves(v) == table[2 * (1 - one) + rpy][integ], (rpy, integ, one, v)
