@@ -458,6 +458,7 @@ inline bool pairs_close(const Dev& d, const Epi& e) {
 hipError_t launch_epilogue(const Dev& d, const Epi& e, hipStream_t s);
 /* steric forces at stage positions Y, then the next pack (steric path) */
 hipError_t launch_steric_pack(const Dev& d, const Coef& c, int prec, hipStream_t s);
-hipError_t launch_record(const Dev& d, double* centres, double* com, hipStream_t s);
+/* maxNb: spheres of the largest system */
+hipError_t launch_record(const Dev& d, int maxNb, double* centres, double* com, hipStream_t s);
 
 }  // namespace ad

@@ -2739,21 +2739,38 @@ __global__ __launch_bounds__(256) void k_steric_pack(Dev d, Coef c, int prec) {
  * the additions. The remaining work-groups write the centres. (One thread per
  * component reading global memory ran at the load latency: 306 us per record
  * at 4096 spheres and 5027 us at 65536, against 24 and 353; 142
- * us for 512 systems of up to 800 spheres, against 9.) */
+ * us for 512 systems of up to 800 spheres, against 9.) BY_THREADS is that form,
+ * for ensembles whose systems are many and small: a work-group costs about 1 ns
+ * of the chip, an addition from memory 0.07 us of its thread, so it is taken
+ * from 64 systems per sphere of the largest one (us per record, work-groups
+ * and threads: 30000 dumbbells 29 and 2, 8192 systems of 16 spheres 11.0 and
+ * 5.4, 4096 6.5 and 4.3; 1024 of 54 3.5 and 11.4). */
 constexpr int REC_WG = 256;
 constexpr int REC_T = 512;  /* spheres per tile */
 constexpr int REC_RS = REC_T + 2; /* LDS row stride: even, so that pairs are 16-byte aligned */
 constexpr int REC_U = 16;   /* additions per batch of LDS reads */
 
+template <int BY_THREADS>
 __global__ __launch_bounds__(REC_WG) void k_record(Dev d, double* __restrict__ centres, double* __restrict__ com,
                                                    int ncom) {
-    __shared__ __align__(16) double tile[2][3][REC_RS];
+    __shared__ __align__(16) double tile[2][3][BY_THREADS ? 2 : REC_RS];
     const int N = d.Ntot;
     if ((int)blockIdx.x >= ncom) {
         const int g = (blockIdx.x - ncom) * REC_WG + threadIdx.x;
         if (centres && g < d.Stot)
             for (int a = 0; a < 3; ++a)
                 centres[3 * g + a] = 0.5 * (d.X[a * N + 2 * g] + d.X[a * N + 2 * g + 1]);
+        return;
+    }
+    if constexpr (BY_THREADS) {
+        const int g = blockIdx.x * REC_WG + threadIdx.x;
+        if (g < 3 * d.nsys) {
+            const int b = g / 3, a = g % 3;
+            const int j0 = d.sys_off[b], j1 = d.sys_off[b + 1];
+            double sum = 0.0;
+            for (int j = j0; j < j1; ++j) sum = sum + d.X[a * N + j];
+            com[3 * b + a] = sum / (double)(j1 - j0);
+        }
         return;
     }
     const int b = blockIdx.x;
@@ -3760,11 +3777,13 @@ hipError_t launch_steric_pack(const Dev& d, const Coef& c, int prec, hipStream_t
     return hipGetLastError();
 }
 
-hipError_t launch_record(const Dev& d, double* centres, double* com, hipStream_t s) {
-    const int ncom = com ? d.nsys : 0;
+hipError_t launch_record(const Dev& d, int maxNb, double* centres, double* com, hipStream_t s) {
+    const bool threads = d.nsys / 64 >= maxNb;
+    const int ncom = !com ? 0 : threads ? (3 * d.nsys + REC_WG - 1) / REC_WG : d.nsys;
     const int ncen = centres ? (d.Stot + REC_WG - 1) / REC_WG : 0;
     if (ncom + ncen == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_record, dim3(ncom + ncen), dim3(REC_WG), 0, s, d, centres, com, ncom);
+    hipLaunchKernelGGL(threads ? k_record<1> : k_record<0>, dim3(ncom + ncen), dim3(REC_WG), 0, s, d, centres, com,
+                       ncom);
     return hipGetLastError();
 }
 

@@ -855,7 +855,7 @@ static int advance(ad_ctx* c, long long nsteps, int record_every, double* centre
             if (record_every > 0 && n % record_every == 0) {
                 double* cp = centres ? centres + rec * 3LL * c->Stot : nullptr;
                 double* mp = com ? com + rec * 3LL * c->nsys : nullptr;
-                HIPCHECK(c, ad::launch_record(c->dev, cp, mp, st));
+                HIPCHECK(c, ad::launch_record(c->dev, c->maxNb, cp, mp, st));
                 ++rec;
             }
         }
