@@ -104,8 +104,8 @@ typedef struct ad_params {
  * AD_FP64 with fused = 0 validates ipl, jchunk, wg and wj but its pair
  * kernel does not use them: a work-group of one or two producer waves and a
  * consumer wave per 2 or 4 target spheres, every source of the system in
- * ascending order (from 4096 systems of 64 spheres or fewer on average a thread
- * per target, where the shape has one). Nor do the steps of AD_FP32C with fused = 0 for one large
+ * ascending order (a thread per target from 4096 systems of 64 spheres or fewer
+ * on average, unless one is so large that the others would wait for it). Nor do the steps of AD_FP32C with fused = 0 for one large
  * system (from 8704 spheres with hi/lo positions or steric forces, 13312 with
  * single floats): their pair kernel forms every unordered pair once.
  * ad_mobility_apply uses the shape in every case. */

@@ -349,8 +349,16 @@ __host__ __device__ inline F64WShape f64w_shape(int Ntot, int rpy, int nsys) {
  * the same bits) is faster from about 4096 systems. us per RK4 step, blocks and
  * threads: 2048 dumbbells 23.5 and 30, 4096 39 and 33, 30000 190 and 108;
  * systems of 16 spheres, 512 24 and 40, 4096 118 and 92; of 64 spheres, 1024
- * 116 and 134, 4096 392 and 275. */
-inline bool f64_by_threads(int nsys, int Ntot) { return nsys >= 4096 && Ntot / nsys <= 64; }
+ * 116 and 134, 4096 392 and 275.
+ * A thread's chain runs over its whole system, about 1 us per sphere and RK4
+ * step, where the blocks (about Ntot / 4 + nsys / 2 of them) take 5.7 ns each
+ * whatever the sizes: the largest system's chain must not outlast them. 4095
+ * systems of 16 spheres and one more, blocks and threads: of 48 spheres 117 and
+ * 102, 64 116 and 112, 96 116 and 132, 4000 319 and 3260; 16000 dumbbells and
+ * one system of 32 spheres 110 and 68, of 128 111 and 141. */
+inline bool f64_by_threads(int nsys, int Ntot, int maxNb) {
+    return nsys >= 4096 && Ntot / nsys <= 64 && maxNb <= (Ntot + 2LL * nsys) / 1024;
+}
 /* LDS of a work-group: two sets of np chunk buffers of rows x (cw + 2) */
 __host__ __device__ inline int f64w_lds_bytes(const F64WShape& f, int rpy) {
     return 2 * f.np * (rpy ? 6 : 3) * f.tw * (f.cw + 2) * 8;

@@ -253,13 +253,9 @@ static int validate_launch(ad_ctx* c, const ad_launch& L) {
 static bool uses_lists(const ad_ctx* c) { return c->p.steric_k != 0.0 && c->p.precision == AD_FP32C; }
 
 /* AD_FP64 with two kernels per stage: by blocks of targets (k_pairs_f64w),
- * unless there are many small systems and the launch shape is one that the
- * thread-per-target kernel has */
+ * unless there are many small systems */
 static bool f64_blocks(const ad_ctx* c) {
-    const ad_launch& L = c->launch;
-    if (c->p.precision != AD_FP64 || L.fused != 0) return false;
-    const bool threads = L.wj == 1 && (L.wg == 64 || L.wg == 256) && (L.ipl == 1 || L.ipl == 2);
-    return !(threads && ad::f64_by_threads(c->nsys, c->Ntot));
+    return c->p.precision == AD_FP64 && c->launch.fused == 0 && !ad::f64_by_threads(c->nsys, c->Ntot, c->maxNb);
 }
 
 static ad::Shape shape_of(const ad_ctx* c) {
