@@ -105,10 +105,13 @@ typedef struct ad_params {
  * kernel does not use them: a work-group of one or two producer waves and a
  * consumer wave per 2 or 4 target spheres, every source of the system in
  * ascending order (a thread per target from 4096 systems of 64 spheres or fewer
- * on average, unless one is so large that the others would wait for it). Nor do the steps of AD_FP32C with fused = 0 for one large
- * system (from 8704 spheres with hi/lo positions or steric forces, 13312 with
- * single floats): their pair kernel forms every unordered pair once.
- * ad_mobility_apply uses the shape in every case. */
+ * on average, unless one is so large that the others would wait for it). Nor
+ * do the steps of AD_FP32C with fused = 0 for one large system (from 8704
+ * spheres with hi/lo positions or steric forces, 13312 with single floats, up
+ * to 585000): their pair kernel forms every unordered pair once. (On a
+ * workspace bound for another shape, which does not hold its partial sums, the
+ * steps use the shape.) ad_mobility_apply uses the shape in AD_FP32C and
+ * AD_FP64_TILED. */
 typedef struct ad_launch {
     int32_t ipl;      /* target spheres per lane: 1, 2 or 4 (FP64 modes: 1 or 2; dense: 1) */
     int32_t jchunk;   /* source spheres per work-group, >= 64 (AD_FP64: whole system;

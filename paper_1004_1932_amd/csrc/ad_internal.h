@@ -268,6 +268,10 @@ hipError_t launch_pairs(const Dev& d, const Epi& e, const Shape& sh, int mode, h
  * the epilogue follows */
 hipError_t launch_pairs_sym(const Dev& d, const Epi& e, const Shape& sh, hipStream_t s,
                             hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+/* Its partial sums take about 12 N^2 / 1024 bytes, where the ordered pair
+ * kernel's take 24 to 100 N: 0.13 GB at 65536 spheres, 13 GB at 2^20, more than
+ * the card from 5 million on. Up to 4 GiB of them. */
+constexpr int SYM_MAX = 585000;
 /* The systems it takes. It saves instructions, most with hi/lo positions and
  * with steric forces (whose other kernel tests every pair's distance), and
  * pays for partial sums at both ends of a pair. us per RK4 step against the
@@ -276,7 +280,7 @@ hipError_t launch_pairs_sym(const Dev& d, const Epi& e, const Shape& sh, hipStre
  * 389 (426); steric, hi/lo 7000 198 (207), 8192 239 (226), 10000 302 (336),
  * 16384 571 (749); steric, single-float 8300 217 (217), 12000 328 (352). */
 inline bool sym_takes(int N, int hilo, int steric) {
-    return N >= (steric || hilo ? 8704 : 13312);
+    return N >= (steric || hilo ? 8704 : 13312) && N <= SYM_MAX;
 }
 /* spheres per block: work-groups of 4 or 8 waves, 128 spheres per wave (the
  * larger block halves the partial sums of the largest systems) */

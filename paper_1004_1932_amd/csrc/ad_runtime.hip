@@ -63,6 +63,7 @@ struct ad_ctx {
     std::vector<long long> sbase; /* and per block its first partial */
     std::vector<int32_t> sP;      /* and number of partial slots */
     long long nspart = 0;         /* its partials in all */
+    bool no_sym = false;          /* the bound workspace does not hold them: the ordered pair sum */
     bool fused_ready = false;     /* the fused kernels may use all of LDS */
     long long nH = 0;             /* dense mode: tensor elements over all systems */
     int maxNb = 0;
@@ -324,7 +325,7 @@ static void build_sym_items(ad_ctx* c) {
     c->sbase.clear();
     c->sP.clear();
     c->nspart = 0;
-    if (c->p.precision != AD_FP32C || c->nsys != 1 || c->launch.fused != 0 ||
+    if (c->no_sym || c->p.precision != AD_FP32C || c->nsys != 1 || c->launch.fused != 0 ||
         !ad::sym_takes(c->Ntot, c->launch.posmode == AD_POS_HILO, c->p.steric_k != 0.0))
         return;
     const int N = c->Ntot, bs = ad::sym_block(N), nb = (N + bs - 1) / bs, nch = (N + 63) / 64, cpb = bs / 64;
@@ -968,6 +969,14 @@ int ad_bind_workspace(ad_ctx* c, void* ptr, uint64_t bytes) {
     if (bytes < layout(c).total)
         return fail(c, AD_ENOMEM, "workspace of %llu bytes, need %llu", (unsigned long long)bytes,
                     (unsigned long long)layout(c).total);
+    if (c->no_sym) { /* the new one may hold them */
+        c->no_sym = false;
+        build_sym_items(c);
+        if (bytes < layout(c).total) {
+            c->no_sym = true;
+            build_sym_items(c);
+        }
+    }
     if (!c->h_tab) {
         HIPCHECK(c, hipHostMalloc((void**)&c->h_tab, (size_t)kRing * 8 * sizeof(double), hipHostMallocDefault));
         HIPCHECK(c, hipHostMalloc((void**)&c->h_phi, (size_t)c->Stot * sizeof(double2), hipHostMallocDefault));
@@ -995,12 +1004,21 @@ int ad_set_launch(ad_ctx* c, const ad_launch* L) {
     if (want.posmode == 0) want.posmode = def.posmode;
     int rc = validate_launch(c, want);
     if (rc != AD_OK) return rc;
-    ad_launch old = c->launch;
+    const ad_launch old = c->launch;
+    const bool old_no_sym = c->no_sym;
     c->launch = want;
+    c->no_sym = false;
     build_items(c);
     if (c->ws) {
         if (layout(c).total > c->ws_bytes) {
+            /* a workspace bound for another form: it need not hold the
+             * symmetric pair sum's partials */
+            c->no_sym = true;
+            build_sym_items(c);
+        }
+        if (layout(c).total > c->ws_bytes) {
             c->launch = old;
+            c->no_sym = old_no_sym;
             build_items(c);
             return fail(c, AD_ENOMEM, "workspace too small for this launch shape");
         }

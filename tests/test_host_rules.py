@@ -52,3 +52,27 @@ def test_fp64_ensembles_take_threads_only_where_no_system_outlasts_the_others(ru
     assert not threads([8] * 4095 + [2000]) and not threads([1] * 4095 + [2000])
     assert not threads([1] * 8191 + [200]) and not threads([20] * 4090 + [200] * 10)
     assert not threads([8] * 4095 + [60]) and not threads([1] * 4095 + [16])
+
+
+def test_symmetric_pair_sum_within_its_sizes(rule):
+    for N in (8704, 65536, 585000):
+        assert rule("sym_takes", N, 1, 0) and rule("sym_takes", N, 0, 1)
+    for N in (8702, 585002, 1 << 20, 1 << 23):
+        assert not rule("sym_takes", N, 1, 0) and not rule("sym_takes", N, 0, 1) and not rule("sym_takes", N, 0, 0)
+
+
+def test_workspace_of_the_largest_systems_grows_linearly():
+    """One FP32C system, default launch: what an ordered pair sum needs. Its
+    partial sums per lower block would be 13 GB at 2^20 spheres."""
+    from paper_1004_1932_amd import binding as B
+    from workload import Params
+
+    def size(N):
+        ctx = B.ad_create(B.make_params(Params(), "fp32c"), [N // 2])
+        n = B.ad_workspace_size(ctx)
+        B.ad_destroy(ctx)
+        return n
+
+    assert size(1 << 20) <= 1000 * (1 << 20)
+    assert size(1 << 21) <= 2.1 * size(1 << 20)
+    assert size(1 << 19) <= 5 << 30
