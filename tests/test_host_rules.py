@@ -76,3 +76,16 @@ def test_workspace_of_the_largest_systems_grows_linearly():
     assert size(1 << 20) <= 1000 * (1 << 20)
     assert size(1 << 21) <= 2.1 * size(1 << 20)
     assert size(1 << 19) <= 5 << 30
+
+
+def test_autotuner_knows_which_steps_the_symmetric_pair_sum_takes(rule):
+    from dataclasses import replace
+
+    from paper_1004_1932_amd import autotune as A
+    from paper_1004_1932_amd import binding as B
+    from workload import Params
+    for N in (8702, 8704, 13310, 13312, 60000, 585000, 585002):
+        for posmode in (B.AD_POS_HILO, B.AD_POS_SINGLE):
+            for ks in (0.0, 1.0):
+                want = rule("sym_takes", N, int(posmode == B.AD_POS_HILO), int(ks != 0.0))
+                assert A.step_ignores_shape(replace(Params(), steric_k=ks), [N // 2], dict(posmode=posmode)) == want
