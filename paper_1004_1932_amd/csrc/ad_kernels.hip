@@ -3518,9 +3518,10 @@ static hipError_t go_f64t(const Dev& d, const Epi& e, const Shape& sh, int mode,
     return hipGetLastError();
 }
 
-template <int TW, int NP, int CW>
+/* RPY: whether the shape is taken with the correction too */
+template <int TW, int NP, int CW, int RPY = 1>
 static hipError_t go_f64w(const Dev& d, const Epi& e, const Shape& sh, int mode, hipStream_t s, const Timing& tm) {
-    auto kern = sh.rpy ? k_pairs_f64w<TW, NP, CW, 1> : k_pairs_f64w<TW, NP, CW, 0>;
+    auto kern = RPY && sh.rpy ? k_pairs_f64w<TW, NP, CW, RPY> : k_pairs_f64w<TW, NP, CW, 0>;
     const size_t lds = f64w_lds_bytes({TW, NP, CW}, sh.rpy);
     const dim3 block(64 * (NP + 1));
     if (tm.start)
@@ -3546,7 +3547,7 @@ hipError_t launch_pairs(const Dev& d, const Epi& e, const Shape& sh, int mode, h
         const F64WShape f = f64w_shape(d.Ntot, sh.rpy, d.nsys);
         if (f.tw == 4 && f.np == 2 && f.cw == 64) return go_f64w<4, 2, 64>(d, e, sh, mode, s, tm);
         if (f.tw == 4 && f.np == 1 && f.cw == 64) return go_f64w<4, 1, 64>(d, e, sh, mode, s, tm);
-        if (f.tw == 4 && f.np == 1 && f.cw == 128 && !sh.rpy) return go_f64w<4, 1, 128>(d, e, sh, mode, s, tm);
+        if (f.tw == 4 && f.np == 1 && f.cw == 128 && !sh.rpy) return go_f64w<4, 1, 128, 0>(d, e, sh, mode, s, tm);
         if (f.tw == 2 && f.np == 2 && f.cw == 64) return go_f64w<2, 2, 64>(d, e, sh, mode, s, tm);
         if (f.tw == 2 && f.np == 1 && f.cw == 128) return go_f64w<2, 1, 128>(d, e, sh, mode, s, tm);
         return hipErrorInvalidValue;
