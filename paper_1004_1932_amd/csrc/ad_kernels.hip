@@ -2049,18 +2049,26 @@ __global__ __launch_bounds__(1024) void k_stage_stream64(Dev d, Epi e) {
  *     1 - s y, after which the quotient is the rounded one (Markstein, "Computation
  *     of elementary functions on the IBM RISC System/6000 processor", 1990)
  *     unless the divisor's significand is all ones;
- *   1/r2 starts from (2h)^2 (within 2^-45): one Newton step, then the quotient
- *     a y corrected once by its residual a - r2 q, rounded under the same
- *     condition on r2.
- * 21 FP64 instructions and one transcendental in place of the compiler's 39
+ *   1/r2 starts from (2h)^2: one Newton step, then the quotient a y corrected
+ *     once by its residual a - r2 q, rounded under the same condition on r2 if
+ *     y is the rounded 1/r2.
+ * y could be another one only where 1/r2 lies within the step's error (2^-88.8
+ * for a v_rsq_f64 anywhere within 2^-23) of a midpoint, and a quotient next to a
+ * midpoint goes wrong by that only for significands 2 - 2t of r2 with t < 2^-36
+ * (for others |r| |y - 1/r2| stays below every quotient's distance from a
+ * midpoint). There 1/r2 is t^2 from the midpoint 1 + t: what remains are the 195
+ * significands 2 - (2k + 1) 2^-52. This chip's v_rsq_f64 is within 2^-26.1 there
+ * (2^-24.1 elsewhere), and of them y is another one for k = 0, left out, and in
+ * one parity k = 1, of which no quotient is that near. (The tests take every k
+ * below 260 with its nearest quotients, and emulate the rest with other seeds;
+ * the compiler's division fails some of them.)
+ * 20 FP64 instructions and one transcendental in place of the compiler's 39
  * and three for the same three values (its square root and divisions also
  * scale the exponents and fix up special operands), and a dependent chain of
  * 15 for both quotients. They hold where no intermediate can leave the normal
  * range: r2 in [2^-400, 2^400) and |fr| zero or in [2^-500, 2^500), and where
  * neither s nor r2 has an all-ones low word; the callers test that (Range64)
- * and take the plain expressions otherwise. (Checked on the CPU with fma for 2.1e9
- * operands, hard cases among them; the parity tests compare whole
- * trajectories.) */
+ * and take the plain expressions otherwise. */
 __device__ __forceinline__ unsigned lo_word(double x) {
     return (unsigned)__builtin_bit_cast(unsigned long long, x);
 }
@@ -2095,9 +2103,9 @@ struct Range64 {
         return (h | lo_word(x)) == 0 || h >= kFrLo;
     }
 };
-/* s = sqrt(x) and ir = 1/s as the plain expressions round them, and y = 1/x (rounded but
- * for rare last-bit cases) for div_exact; ones is raised to 0xffffffff where
- * the short forms do not hold (s or x with an all-ones low word) */
+/* s = sqrt(x) and ir = 1/s as the plain expressions round them, and y = 1/x
+ * (rounded where ones allows the short forms) for div_exact; ones is raised to
+ * the low words of s and x */
 __device__ __forceinline__ void rcp_sqrt_exact(double x, double& s, double& ir, double& y, unsigned& ones) {
     const double v = __builtin_amdgcn_rsq(x);
     double g = x * v;
