@@ -218,7 +218,7 @@ __device__ __forceinline__ int add_steric(const Dev& d, const Coef& c, int s, in
                 const int o = lane - 3 * q;
                 const double2* v = reinterpret_cast<const double2*>(row[o < 0 ? 0 : o > 5 ? 5 : o]);
                 double sum = acc;
-#pragma unroll 8
+#pragma unroll 4
                 for (int k = 0; k < 32; ++k) {
                     sum = sum + v[k].x;
                     sum = sum + v[k].y;

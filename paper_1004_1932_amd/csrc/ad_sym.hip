@@ -255,10 +255,11 @@ __global__ __launch_bounds__(64 * NW) void k_pairs_sym(Dev d, Epi e) {
 #pragma unroll
                         for (int q = 0; q < IPL; ++q) {
                             float rx, ry, rz;
-                            const int j = c * 64 + row * 16 + (at & 15);
-                            /* lanes and entries past the end stand far off, but not
-                             * out of reach where lengths are near 1e15 */
-                            if (separation(q, A, B, rx, ry, rz) < d.list_r2 && ib + q < N && j < N) {
+                            if (separation(q, A, B, rx, ry, rz) < d.list_r2) {
+                                const int j = c * 64 + row * 16 + (at & 15);
+                                /* lanes and entries past the end stand far off, but not
+                                 * out of reach where lengths are near 1e15 */
+                                if (ib + q >= N || j >= N) continue;
                                 append(d.nbr_cnt, d.nbr_idx, &d.ctl->flag, ib + q, j);
                                 append(d.nbr_cnt, d.nbr_idx, &d.ctl->flag, j, ib + q);
                             }
