@@ -127,10 +127,10 @@ typedef struct ad_launch {
                          2: the same with 64 target spheres per 4-wave work-group, one per
                          lane, for ensembles of small systems (at most 6824 single-float or
                          4548 hi/lo spheres per system);
-                         3: 4, 8 or 16 target spheres per work-group (about N_total / 256)
+                         3: 4 target spheres per work-group up to N_total 1024, 8 below 4096, else 16,
                          whose waves stream their share of the sources through a small LDS
                          slot each (AD_FP32C, or AD_FP64_TILED in FP64 arithmetic with
-                         v_rsq_f64 refined by one Newton step and FMAs; no steric forces, any
+                         v_rsq_f64 refined by one third-order step and FMAs; no steric forces, any
                          system size; sources are padded to a multiple of 1024);
                          4: resident: one work-group per system keeps the whole system on
                          the compute unit and runs every stage of a run of steps (up to the

@@ -67,10 +67,11 @@ def tuned_launch(S_per_sys, path: Path = TABLE):
 # stage of a run of steps in one launch; bitwise the same sums as the
 # form with a launch per stage) up to this many spheres per system: us per
 # AD_FP64 step, resident and a launch per stage replayed from graphs, 16 spheres
-# 3.9 and 13.2, 32 9.3 and 13.6, 512 lattices of 27 dumbbells 32 and 62. Its
-# term chunks become long sequential loops per thread as systems grow: of a
-# single system of 54 spheres it takes 23 us (13.6 replayed; launched one by
-# one, a stage's launch alone is about 5).
+# 3.9 and 13.2, 32 9.3 and 13.6, 512 lattices of 27 dumbbells 32 and 62. The
+# rule looks at the size alone and is kept for such ensembles. Its term chunks
+# become long sequential loops per thread as systems grow, so a single system
+# near the limit is slower in it: 54 spheres 23 us and 15 with a launch per
+# stage, 64 spheres 31 and 15.
 RESIDENT_FP64_MAX = 64
 RESIDENT_FP64 = {"ipl": 1, "jchunk": 128, "wg": 64, "wj": 1, "posmode": 0, "fused": 4}
 

@@ -626,8 +626,8 @@ constexpr int EPI_MAXP = 16; /* partials loaded per batch */
 
 /* p[0] + p[stride] + ... of P partial sums, in order: the loads of a batch go
  * ahead of its additions (one product of 6000 spheres with RPY, whose second
- * sum was added load by load: 73 us, 68 this way; batches of 32 and 64 are no
- * faster). */
+ * sum was added load by load: 65.4 us, 59.6 this way; batches of 32 and 64 are
+ * no faster). */
 __device__ __forceinline__ double sum_slots(const double* p, long long stride, int P) {
     double v[EPI_MAXP];
 #pragma unroll
@@ -2420,9 +2420,9 @@ __device__ __forceinline__ void lds_barrier() {
  * The terms are the plain sum's expressions and the additions its sequence,
  * so the result is bitwise k_pairs_f64's with one chunk per system. The
  * self term, a coincident pair (which raises the flag) and the padding past
- * the system's last source are stored as +0.0 and added like the others: a
- * sum that starts at +0.0 is never -0.0 in round-to-nearest, so adding +0.0
- * changes no bit of it. The consumer's lanes past the last row repeat its
+ * the system's last source are stored as zeros of either sign and added like
+ * the others: a sum that starts at +0.0 is never -0.0 in round-to-nearest, so
+ * adding +0.0 or -0.0 changes no bit of it. The consumer's lanes past the last row repeat its
  * reads and additions (the same LDS addresses, served once). */
 template <int TW, int NP, int CW, int RPY>
 __global__ __launch_bounds__(64 * (NP + 1)) void k_pairs_f64w(Dev d, Epi e, int mode) {
@@ -3112,9 +3112,9 @@ __global__ __launch_bounds__(RES_T, !ONE && RPY && INTEG == 2 ? 4 : 1) void k_re
             for (int q = tid; q < 3 * n; q += T) {
                 const double* row = Tm + q * cs; /* component q / n of target q mod n */
                 const double* rowb = Tb + q * cs;
-                /* The self term was stored as +0.0 and is added like the
+                /* The self term was stored as a zero and is added like the
                  * others: a sum that starts at +0.0 is never -0.0 in
-                 * round-to-nearest, so adding +0.0 leaves it unchanged, bit
+                 * round-to-nearest, so adding a zero leaves it unchanged, bit
                  * for bit the sum that skips j = i. */
                 double acc = (j0 == 0) ? 0.0 : Acc[q];
                 double bcc = (RPY && j0 > 0) ? Bcc[q] : 0.0;
